@@ -11,8 +11,8 @@ left as None are read from the device tensors with .item(), which waits for the
 GPU: such a call is neither asynchronous nor capturable into a HIP graph. Pass
 them explicitly (and an output and workspace) to capture a call or to keep it
 asynchronous. With stream= given, outputs and workspaces the wrapper allocates
-are recorded on that stream, so torch does not reuse their memory before the
-call's kernels finish.
+come from that stream's own memory, so neither earlier work of other streams nor
+a later reuse of the memory can overlap the call's kernels.
 
 Layout (see the header): K pool [pages][Hkv][16][128] (token-major), V pool
 [pages][Hkv][128][16] (dim-major), block table int32 [B][stride]. Pools are
@@ -72,20 +72,27 @@ def _stream(device: torch.device, stream) -> int:
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
-def _empty(shape, dtype: torch.dtype, device: torch.device, stream) -> torch.Tensor:
-    """torch.empty for an output or workspace of a call launched on `stream`.
+def _empty(shape, dtype: torch.dtype, device: torch.device, stream,
+           scratch: bool = False) -> torch.Tensor:
+    """torch.empty for an output or workspace (scratch) of a call launched on `stream`.
 
-    torch's caching allocator ties a block to the stream that was current when it
-    was allocated. When the call runs on another stream (stream= given), the block
-    is also recorded on that stream, so that it is not handed to new work before
-    the call's kernels are done with it (a workspace the wrapper drops on return
-    would otherwise be reusable at once by work on the current stream)."""
-    t = torch.empty(shape, dtype=dtype, device=device)
-    if stream is not None:
-        s = stream if isinstance(stream, torch.cuda.Stream) else \
-            torch.cuda.ExternalStream(int(stream), device=device)
-        if s.cuda_stream != torch.cuda.current_stream(device).cuda_stream:
-            t.record_stream(s)
+    torch's caching allocator orders the reuse of a block by the stream that was
+    current when it was allocated: a block freed there may still have that stream's
+    work pending on it when it is handed out again. When the call runs on another
+    stream (stream= given), the block is therefore allocated as that stream's own, so
+    that everything pending on it comes before the call's kernels; an output is also
+    recorded on the current stream, where the caller may read it before dropping it."""
+    if stream is None:
+        return torch.empty(shape, dtype=dtype, device=device)
+    s = stream if isinstance(stream, torch.cuda.Stream) else \
+        torch.cuda.ExternalStream(int(stream), device=device)
+    current = torch.cuda.current_stream(device)
+    if s.cuda_stream == current.cuda_stream:
+        return torch.empty(shape, dtype=dtype, device=device)
+    with torch.cuda.stream(s):
+        t = torch.empty(shape, dtype=dtype, device=device)
+    if not scratch:
+        t.record_stream(current)
     return t
 
 
@@ -174,7 +181,7 @@ def decode(q: torch.Tensor, kv: PagedKV, kv_lens: torch.Tensor, max_kv_len: Opti
         _shape(lse, (B, Hq), "lse")
     ws_bytes = lib.rollout_attn_decode_workspace_size(B, Hq, kv.num_kv_heads, max_kv_len)
     if workspace is None:
-        workspace = _empty(max(ws_bytes, 1), torch.uint8, dev, stream)
+        workspace = _empty(max(ws_bytes, 1), torch.uint8, dev, stream, scratch=True)
     _need(workspace, "workspace", torch.uint8, dev)
     s = kv.struct()
     _lib.check("rollout_attn_decode", lib.rollout_attn_decode(
@@ -260,7 +267,7 @@ def decode_shared_prefix(q: torch.Tensor, kv: PagedKV, kv_lens: torch.Tensor,
     ws_bytes = lib.rollout_attn_decode_shared_prefix_workspace_size(
         B, Hq, kv.num_kv_heads, max_kv_len, max_prefix_len)
     if workspace is None:
-        workspace = _empty(max(ws_bytes, 1), torch.uint8, dev, stream)
+        workspace = _empty(max(ws_bytes, 1), torch.uint8, dev, stream, scratch=True)
     _need(workspace, "workspace", torch.uint8, dev)
     s = kv.struct()
     _lib.check("rollout_attn_decode_shared_prefix", lib.rollout_attn_decode_shared_prefix(
@@ -307,7 +314,7 @@ def append(q: torch.Tensor, cu_q: torch.Tensor, ctx_lens: torch.Tensor, kv: Page
         _shape(lse, (total_q, Hq), "lse")
     ws_bytes = lib.rollout_attn_append_workspace_size(B, Hq, kv.num_kv_heads, max_q_len)
     if workspace is None:
-        workspace = _empty(max(ws_bytes, 1), torch.uint8, dev, stream)
+        workspace = _empty(max(ws_bytes, 1), torch.uint8, dev, stream, scratch=True)
     _need(workspace, "workspace", torch.uint8, dev)
     s = kv.struct()
     _lib.check("rollout_attn_append", lib.rollout_attn_append(
@@ -360,7 +367,7 @@ def append_write(q: torch.Tensor, k_new: torch.Tensor, v_new: torch.Tensor, cu_q
         _shape(lse, (total_q, Hq), "lse")
     ws_bytes = lib.rollout_attn_append_workspace_size(B, Hq, kv.num_kv_heads, max_q_len)
     if workspace is None:
-        workspace = _empty(max(ws_bytes, 1), torch.uint8, dev, stream)
+        workspace = _empty(max(ws_bytes, 1), torch.uint8, dev, stream, scratch=True)
     _need(workspace, "workspace", torch.uint8, dev)
     s = kv.struct()
     if cos_sin is None:
@@ -446,7 +453,7 @@ def mixed(q_decode: torch.Tensor, kv_decode: PagedKV, kv_lens: torch.Tensor,
         Bd, Ba, Hq, kv_decode.num_kv_heads, kv_append.num_kv_heads, max_kv_len_decode,
         max_q_len)
     if workspace is None:
-        workspace = _empty(max(ws_bytes, 1), torch.uint8, dev, stream)
+        workspace = _empty(max(ws_bytes, 1), torch.uint8, dev, stream, scratch=True)
     _need(workspace, "workspace", torch.uint8, dev)
     sd, sa = kv_decode.struct(), kv_append.struct()
     _lib.check("rollout_attn_mixed", lib.rollout_attn_mixed(
@@ -564,7 +571,7 @@ def _token_logprob(h, W, targets, scale, out, lse, want_lse, workspace, stream, 
         _shape(lse, (N,), "lse")
     if workspace is None:
         workspace = _empty(max(lib.token_logprob_workspace_size(N, V, D), 1), torch.uint8, dev,
-                           stream)
+                           stream, scratch=True)
     _need(workspace, "workspace", torch.uint8, dev)
     fn = lib.token_logprob if packed_V is None else lib.token_logprob_packed
     name = "token_logprob" if packed_V is None else "token_logprob_packed"
