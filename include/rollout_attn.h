@@ -237,12 +237,14 @@ int rollout_attn_decode_shared_prefix(const void *q, const ra_paged_kv *kv,
  *   lse         fp32 [total_q][Hq] or NULL
  *   workspace   device scratch of at least
  *               rollout_attn_append_workspace_size(B, Hq, Hkv, max_q_len) bytes
- *               (the call's work list and counter, rewritten by every call;
- *               contents on entry are ignored). Calls that share a workspace
- *               must not overlap.
+ *               (the call's work lists, counters and partial results, some 68
+ *               MB, rewritten by every call; contents on entry are ignored).
+ *               Calls that share a workspace must not overlap.
  * The work is planned on the device (a one-workgroup kernel orders the rows
- * longest first and queues each KV head's tiles for one XCD) and run by one
- * persistent workgroup per CU.
+ * longest first and queues each KV head's tiles for one XCD, or, with too few
+ * tiles to fill the GPU, cuts their key ranges into equal shares whose partial
+ * results are merged) and run by one persistent workgroup per CU. Neither the
+ * order nor the cuts depend on anything but the rows' lengths.
  * Errors as for decode; RA_ERR_UNSUPPORTED also for more than 256 KV heads.
  */
 size_t rollout_attn_append_workspace_size(int32_t B, int32_t Hq, int32_t Hkv,
@@ -346,8 +348,8 @@ int rollout_attn_append_write_rope(const void *q, const void *k_new, const void 
  *   Hq, scale     shared by both sides
  *   workspace     device scratch of at least rollout_attn_mixed_workspace_size(
  *                 B_decode, B_append, Hq, Hkv_decode, Hkv_append,
- *                 max_kv_len_decode, max_q_len) bytes: work lists, a work
- *                 counter and decode partials, all rewritten by every call
+ *                 max_kv_len_decode, max_q_len) bytes: work lists, work
+ *                 counters and partial results, all rewritten by every call
  *                 (contents on entry are ignored). Calls that share a
  *                 workspace must not overlap.
  * Errors: as rollout_attn_decode / rollout_attn_append for each non-empty

@@ -100,6 +100,7 @@ __device__ __forceinline__ int v_lds(int page, int d, int half) {
 
 // LDS of one tile: a ring of four K and V blocks (block B in buffer B % 4).
 constexpr int kBuffers = 4;
+__device__ __forceinline__ int buffer(int block) { return block & (kBuffers - 1); }
 struct AppendLds {
   __attribute__((aligned(16))) uint16_t k[kBuffers * kKBlockElems];
   __attribute__((aligned(16))) uint16_t v[kBuffers * kBlockElems];
@@ -127,29 +128,55 @@ __device__ __forceinline__ int append_tile_blocks(const AppendArgs &a, const App
   return (r.ctx + min(r.T, i0 + a.q_per_block) + kBlock - 1) / kBlock;
 }
 
-// One tile: query block qblk of row b, KV head g, by a workgroup of kThreads
-// threads. Every thread of the workgroup calls it with the same arguments.
+// One tile as the plan lists it: row, query block, its key blocks, and the
+// row's extent.
+struct AppendTile {
+  int row, qblk, blocks, cu0, T, ctx;
+  int pad[2];
+};
+static_assert(sizeof(AppendTile) == 32, "two 16-byte loads");
+__device__ __forceinline__ AppendTile make_tile(const AppendArgs &a, const AppendRow &r, int b,
+                                                int qblk) {
+  return AppendTile{b, qblk, append_tile_blocks(a, r, qblk), r.cu0, r.T, r.ctx, {0, 0}};
+}
+
+// Partial result of a piece of a tile (some of its key blocks): O before the
+// normalisation and (running max, sum) per query row. A row with no key in the
+// piece has sum 0 and max -inf.
+struct PartialOut {
+  float *o;     // [slot][256 query rows][128]
+  float2 *ml;   // [slot][256 query rows]
+};
+
+// One tile, or a piece of it: KV head g, key blocks [kb0, kb1), by a workgroup
+// of kThreads threads. Every thread of the workgroup calls it with the same
+// arguments. slot >= 0: the piece's result goes to that slot of `part`;
+// otherwise the piece is the whole tile and the result is final. next_issue()
+// is called by wave 0 before its masked key blocks (the last few) and its value
+// handed to next_commit() after them, so that what it loads has arrived by then.
 // kFp8: the pools hold E4M3 codes; the staging converts them exactly to bf16
 // on their way into LDS, so everything after the staging is the bf16 tile.
 // kRope: q is rotated at its position (table a.cos_sin) after it is loaded.
-template <bool kPosScale, bool kFp8 = false, bool kRope = false>
-__device__ __forceinline__ void append_tile(const AppendArgs &a, int qblk, int g, int b,
-                                            AppendLds &lds) {
-  const int tid = threadIdx.x;
+template <bool kPosScale, bool kFp8 = false, bool kRope = false, typename Issue,
+          typename Commit>
+__device__ __forceinline__ void append_tile(const AppendArgs &a, const AppendTile &tile, int g,
+                                            int kb0, int kb1, int slot, const PartialOut &part,
+                                            AppendLds &lds, Issue next_issue, Commit next_commit) {
+  // an opaque copy: what follows from it is worked out per tile instead of
+  // being kept in registers (or spilled) across the caller's loop over tiles
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
   const int lane = tid & (kWave - 1), wave = tid / kWave;
   const int col = lane & 31, grp = lane >> 5;
   const int G = a.group, QB = a.q_per_block;
 
-  const AppendRow row_ext = append_row(a, b);
-  const int cu0 = row_ext.cu0, T = row_ext.T, ctx = row_ext.ctx;
-  const int i0 = qblk * QB;
-  if (i0 >= T || ctx < 0) return;
+  const int cu0 = tile.cu0, T = tile.T, ctx = tile.ctx;
+  const int i0 = tile.qblk * QB;
   const int i_end = min(T, i0 + QB);
   const int row_end = ctx + T;                 // keys present in the cache for this row
-  const int kv_end = ctx + i_end;              // keys this workgroup attends to
   const int row_pages = (row_end + kPage - 1) / kPage;
-  const int nblocks = (kv_end + kBlock - 1) / kBlock;
-  const int32_t *bt = a.block_table + (size_t)b * a.bt_stride;
+  const int nblocks = kb1;                     // key blocks kb0 .. nblocks - 1
+  const int32_t *bt = a.block_table + (size_t)tile.row * a.bt_stride;
   const size_t head_stride = (size_t)kPage * kHeadDim;
 
   uint16_t *const sK = lds.k;
@@ -186,6 +213,8 @@ __device__ __forceinline__ void append_tile(const AppendArgs &a, int qblk, int g
   }
   // First query position of this wave (its rows are query-major).
   const int wave_q0 = ctx + i0 + (wave * kRowsPerWave) / G;
+  const bool wave_live = __builtin_amdgcn_readfirstlane(
+      wave * kRowsPerWave < QB * G && i0 + (wave * kRowsPerWave) / G < i_end);
 
   // ---- staging: pass p moves pages 2p, 2p + 1 of the block; each thread one
   // 16-byte chunk of K and one of V. The page index is wave-uniform (waves
@@ -200,24 +229,40 @@ __device__ __forceinline__ void append_tile(const AppendArgs &a, int qblk, int g
   // row (all 16 slots).
   const int f_page = __builtin_amdgcn_readfirstlane(tid >> 7), f_idx = tid & 127;
   const int f_slot = f_idx >> 3, f_c16 = f_idx & 7;
+  // Page ids: lane i of `ids` holds page 64 w + i of the current window of 64
+  // pages (16 blocks), `ids_next` the next window's, requested 16 blocks before
+  // use. A block's ids are then two v_readlane, and its page addresses scalar:
+  // read from the block table at the start of the block, each of them was a
+  // dependent load that all eight waves waited for.
+  auto load_ids = [&](int first) __attribute__((always_inline)) {
+    const int p = first + lane;
+    return clamp_page(bt[p < row_pages ? p : 0], a.num_pages);
+  };
+  const int first_window = kb0 * kBlockPages / kWave * kWave;
+  int ids = load_ids(first_window), ids_next = load_ids(first_window + kWave);
+  const uint32_t k_off = st_slot * kHeadDim + st_kch * 8, v_off = st_d * kPage + st_half * 8;
+  const uint32_t f_koff = f_slot * kHeadDim + f_c16 * 16, f_voff = f_idx * kPage;
   auto stage_load = [&](int blk) __attribute__((always_inline)) {
+    const int pg0 = blk * kBlockPages, w = pg0 % kWave;
+    if (w == 0 && blk != kb0) {
+      ids = ids_next;
+      ids_next = load_ids(pg0 + kWave);
+    }
     if constexpr (kFp8) {
-      const int pgi = blk * kBlockPages + f_page;
-      const int id = clamp_page(pgi < row_pages ? bt[pgi] : bt[0], a.num_pages);
+      const int id = __builtin_amdgcn_readlane(ids, w + f_page);
       const size_t base = ((size_t)id * a.hkv + g) * head_stride;   // bytes
       kreg[0] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const uint8_t *>(a.k_pool) +
-                                                 base + f_slot * kHeadDim + f_c16 * 16);
+                                                 base + f_koff);
       vreg[0] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const uint8_t *>(a.v_pool) +
-                                                 base + f_idx * kPage);
+                                                 base + f_voff);
       return;
     }
 #pragma unroll
     for (int p = 0; p < kPasses; ++p) {
-      const int pgi = blk * kBlockPages + p * kPagesPerPass + st_page;
-      const int id = clamp_page(pgi < row_pages ? bt[pgi] : bt[0], a.num_pages);
+      const int id = __builtin_amdgcn_readlane(ids, w + p * kPagesPerPass + st_page);
       const size_t base = ((size_t)id * a.hkv + g) * head_stride;
-      kreg[p] = load_u32x4(a.k_pool + base + st_slot * kHeadDim + st_kch * 8);
-      vreg[p] = load_u32x4(a.v_pool + base + st_d * kPage + st_half * 8);
+      kreg[p] = load_u32x4(a.k_pool + base + k_off);
+      vreg[p] = load_u32x4(a.v_pool + base + v_off);
     }
   };
   auto stage_store = [&](int blk, int buf) __attribute__((always_inline)) {
@@ -295,20 +340,30 @@ __device__ __forceinline__ void append_tile(const AppendArgs &a, int qblk, int g
   // scores of pair p + 1, none of which depends on it. Blocks of 64 keys
   // rotate through four LDS buffers: while block B is computed, block B - 1
   // is still read (V of its last pair), block B + 1 is complete (keys of the
-  // look-ahead scores) and block B + 2 is being stored. Block -1 (the last
-  // buffer) holds zero V operands (its second pair) for the first step's P·V,
-  // whose weights are zero too.
+  // look-ahead scores) and block B + 2 is being stored. The buffer before the
+  // first block's holds zero V operands (its second pair) for the first
+  // step's P·V, whose weights are zero too.
   static_assert(kThreads * 8 == kBlockElems / 2, "one 16-byte store per thread");
-  *reinterpret_cast<u32x4 *>(&sV[(kBuffers - 1) * kBlockElems + kBlockElems / 2 + 8 * tid]) =
-      u32x4{};
-  stage_load(0);
-  stage_store(0, 0);
-  if (nblocks > 1) {
-    stage_load(1);
-    stage_store(1, 1);
+  *reinterpret_cast<u32x4 *>(
+      &sV[buffer(kb0 + kBuffers - 1) * kBlockElems + kBlockElems / 2 + 8 * tid]) = u32x4{};
+  stage_load(kb0);
+  stage_store(kb0, buffer(kb0));
+  if (kb0 + 1 < nblocks) {
+    stage_load(kb0 + 1);
+    stage_store(kb0 + 1, buffer(kb0 + 1));
   }
   __syncthreads();
-  f32x16 st = scores(0, 0);
+  if (!wave_live) {   // a wave without queries only stages (same barriers, one per block)
+    for (int blk = kb0; blk < nblocks; ++blk) {
+      if (blk + 2 < nblocks) {
+        stage_load(blk + 2);
+        stage_store(blk + 2, buffer(blk + 2));
+      }
+      __syncthreads();
+    }
+    return;
+  }
+  f32x16 st = scores(buffer(kb0), 0);
   bf16x8 pb0 = bf16x8{}, pb1 = bf16x8{};   // weights of the previous pair (none yet)
 
   // P·V of pair pp of the block in buffer buf, weights pb0, pb1:
@@ -390,39 +445,57 @@ __device__ __forceinline__ void append_tile(const AppendArgs &a, int qblk, int g
   };
 
   auto block = [&](int blk, auto mask_tag) __attribute__((always_inline)) {
-    const int bcur = blk % kBuffers, bprev = (blk + kBuffers - 1) % kBuffers,
-              bnext = (blk + 1) % kBuffers;
+    const int bcur = buffer(blk), bprev = buffer(blk + kBuffers - 1), bnext = buffer(blk + 1);
     if (blk + 2 < nblocks) stage_load(blk + 2);
     const int key0 = blk * kBlock;
     step(bprev, 1, bcur, 1, 0, key0, mask_tag);
     step(bcur, 0, bnext, 0, 1, key0, mask_tag);
-    if (blk + 2 < nblocks) stage_store(blk + 2, (blk + 2) % kBuffers);
+    if (blk + 2 < nblocks) stage_store(blk + 2, buffer(blk + 2));
     __syncthreads();
   };
   // Blocks from mb on reach past the wave's first query and take the causal
   // mask; every wave passes the same barriers (one per block).
   const int mb = __builtin_amdgcn_readfirstlane(min(nblocks, (wave_q0 + 1) / kBlock));
-  int blk = 0;
+  int blk = kb0;
   for (; blk < mb; ++blk) block(blk, std::false_type{});
+  const bool first_wave = __builtin_amdgcn_readfirstlane(wave) == 0;
+  int next = 0;
+  if (first_wave) next = next_issue();
   for (; blk < nblocks; ++blk) block(blk, std::true_type{});
-  pv((nblocks - 1) % kBuffers, 1);   // the last pair
+  pv(buffer(nblocks - 1), 1);   // the last pair
+  if (first_wave) next_commit(next);
 
-  // ---- epilogue: normalise and store; lane holds d = 32 dt + 8 (r/4) + 4 grp + r%4 ----
+  // ---- epilogue: normalise and store; lane holds d = 32 dt + 8 (r/4) + 4 grp + r%4.
+  // The thread's query row is worked out again from an opaque copy of its id,
+  // so that none of it is kept in registers through the key loop.
   const float l = l_run + __shfl_xor(l_run, 32);
-  if (qpos >= 0) {
-    const size_t row = (size_t)(cu0 + i0 + qi) * a.hq + (size_t)g * G + hh;
-    const float inv = (kFp8 ? a.v_scale : 1.f) / l;
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-      for (int rq = 0; rq < 4; ++rq) {
-        f32x4 v;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = o[dt][4 * rq + e] * inv;
-        *reinterpret_cast<f32x4 *>(&a.out[row * kHeadDim + 32 * dt + 8 * rq + 4 * grp]) = v;
-      }
-    if (a.lse && grp == 0) a.lse[row] = (m_run + __log2f(l)) * kLn2;
+  int tid_e = tid;
+  asm volatile("" : "+v"(tid_e));
+  const int grp_e = (tid_e >> 5) & 1;
+  const int r_e = tid_e / kWave * kRowsPerWave + (tid_e & 31);
+  const int qi_e = r_e / G;
+  if (r_e >= QB * G || i0 + qi_e >= i_end) return;
+  float inv = (kFp8 ? a.v_scale : 1.f) / l;
+  float *dst;
+  if (slot >= 0) {
+    const size_t prow = (size_t)slot * kRowsPerGroup + r_e;
+    dst = part.o + prow * kHeadDim;
+    inv = 1.f;
+    if (grp_e == 0) part.ml[prow] = make_float2(l > 0.f ? m_run : -INFINITY, l);
+  } else {
+    const size_t row = (size_t)(cu0 + i0 + qi_e) * a.hq + (size_t)g * G + (r_e - qi_e * G);
+    dst = a.out + row * kHeadDim;
+    if (a.lse && grp_e == 0) a.lse[row] = (m_run + __log2f(l)) * kLn2;
   }
+#pragma unroll
+  for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+    for (int rq = 0; rq < 4; ++rq) {
+      f32x4 v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = o[dt][4 * rq + e] * inv;
+      *reinterpret_cast<f32x4 *>(&dst[32 * dt + 8 * rq + 4 * grp_e]) = v;
+    }
 }
 
 // Kernel arguments of an append call (validated by the ABI layer).

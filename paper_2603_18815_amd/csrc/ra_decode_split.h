@@ -129,11 +129,15 @@ __device__ __forceinline__ void decode_split(const DecodeArgs &a, int g, int spl
     }
   }
   if (nr <= 0 || t0 >= t1) return;
-  const int lane = threadIdx.x & (kWave - 1);
+  int tid = threadIdx.x;
+  // in the mixed kernel's loop over entries an opaque copy, so that nothing
+  // that follows from it is kept in registers through the append tiles
+  if constexpr (kW == 8) asm volatile("" : "+v"(tid));
+  const int lane = tid & (kWave - 1);
   // wave-uniform (an SGPR), so that the pair loop and its block-table reads
   // run on the scalar unit instead of as vector loads that each wait for
   // every load issued before them
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int npairs = (t1 - t0 + kPairTokens - 1) / kPairTokens;
   const int row_pages = (t1 + kPage - 1) / kPage;   // pages of row krow in use up to t1
   const int32_t *bt = a.block_table + (size_t)krow * a.bt_stride;
@@ -323,7 +327,7 @@ __device__ __forceinline__ void decode_split(const DecodeArgs &a, int g, int spl
   __syncthreads();
 
   const int ncols = min(nr * G, 16 * NT);
-  for (int idx = threadIdx.x; idx < ncols * kHeadDim; idx += kW * kWave) {
+  for (int idx = tid; idx < ncols * kHeadDim; idx += kW * kWave) {
     const int c = idx / kHeadDim, d = idx % kHeadDim;
     float M = s_m[0][c];
 #pragma unroll

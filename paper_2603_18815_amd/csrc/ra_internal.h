@@ -58,15 +58,17 @@ hipError_t launch_decode_shared_prefix(const uint16_t *q, const PagedKV &kv,
 
 // ---- append, and the mixed step (decode rows and append rows), in one
 // planned persistent launch; append alone is the mixed step without decode
-// rows. Workspace: a header, the append row order, the append tile list, the
-// decode split list and the decode partial results, each at a 256-byte
-// aligned offset.
+// rows. Workspace: a header, the cuts of the tile line, the append row order,
+// the append tile list and its key-block starts, the decode split starts, the
+// decode partial results and the partial results of cut append tiles, each at
+// a 256-byte aligned offset.
 struct MixedLayout {
   DecodePlan plan;            // decode splits
   int32_t qblocks;            // query blocks of the longest append chunk
   int64_t max_tiles;          // bound on append tile entries
   int64_t max_splits;         // bound on decode split entries
-  size_t tiles_offset, splits_offset, partials_offset, bytes;
+  size_t order_offset, tiles_offset, starts_offset, splits_offset, partials_offset;
+  size_t pieces_offset, bytes;
 };
 MixedLayout mixed_layout(int32_t B_decode, int32_t B_append, int32_t hq, int32_t hkv_decode,
                          int32_t hkv_append, int32_t max_kv_len_decode, int32_t max_q_len);

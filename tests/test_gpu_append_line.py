@@ -1,0 +1,76 @@
+"""GPU parity of the append when few tiles are cut into equal shares of key blocks.
+
+With fewer, longer tiles than fill the GPU, the append cuts the key blocks of all
+(KV head, query block) tiles into equal shares and merges the pieces of a tile
+(any call here whose longest tile is over 16 blocks of 64 keys longer than a
+share). The cases put share ends inside tiles, at their ends and across KV heads,
+leave waves and whole query blocks without queries, and cover group sizes from 1
+to 32; each is compared with the fp64 oracle, and the mixed call's append part
+must be bitwise the same. Pieces are merged in fp32, so the attention tolerance
+of tests.gpu_util holds unchanged.
+"""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2603_18815_amd as ra
+import synth
+from tests.gpu_util import APPEND_LSE_ATOL, assert_attn_close, bits
+
+pytestmark = pytest.mark.gpu
+SCALE = 1.0 / math.sqrt(128)
+
+
+def i32(x, dev):
+    return torch.as_tensor(np.ascontiguousarray(np.asarray(x, np.int32)), device=dev)
+
+
+# (Hq, Hkv, ctx, T): 17 blocks in one tile up to many tiles per row
+CASES = [
+    (8, 2, [1088], [1]),                       # two tiles of 18 blocks, one query each
+    (32, 8, [4000], [65]),                     # a second query block with one query
+    (32, 8, [4096 - 64], [64]),                # whole blocks: shares end at tile ends
+    (8, 8, [5000], [257]),                     # groups of one: 256 queries per tile
+    (32, 1, [3000], [20]),                     # groups of 32: 8 queries per tile
+    (15, 3, [2500, 1800], [52, 7]),            # groups of 5 (51 per tile), 3 KV heads
+    (32, 8, [6000, 0, 40, 3000], [3, 70, 0, 1]),   # short, context-free and empty rows among them
+    (4, 1, [20000], [16]),                     # one tile of 313 blocks over all shares
+]
+
+
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("Hq,Hkv,ctx,T", CASES)
+def test_cut_tiles_vs_oracle(device, Hq, Hkv, ctx, T, fp8):
+    print(f"[gpu-test] append line Hq={Hq} Hkv={Hkv} ctx={ctx} T={T} fp8={fp8}", flush=True)
+    w = synth.append_workload(17, len(T), Hq, Hkv, lambda r, n: np.asarray(ctx),
+                              lambda r, n: np.asarray(T), "append line")
+    t = synth.make_tensors(w, device)
+    k, v, scales = t.k_pool, t.v_pool, ()
+    if fp8:
+        gen = synth.value_generator(18, device)
+        scales = (0.02, 0.015)
+        k = synth.randn_fp8_codes(t.k_pool.shape, gen, device, scales[0])
+        v = synth.randn_fp8_codes(t.v_pool.shape, gen, device, scales[1])
+    kv = ra.PagedKV(k, v, i32(w.append_table(), device), *scales)
+    synth.poison_unowned(k, v, w.layout, rows=w.append_rows, lens=w.ctx_lens + w.q_lens)
+    args = (t.q_append, i32(w.cu_q(), device), i32(w.ctx_lens, device))
+    mq, mk = max(T), int(max(c + n for c, n in zip(ctx, T)))
+    out, lse = ra.append(*args, kv, mq, mk, SCALE, want_lse=True)
+    again, _ = ra.append(*args, kv, mq, mk, SCALE)
+    # one decode row over the first row's cache, beside the same append rows
+    od, oa, _, la = ra.mixed(t.q_append[:1], kv, i32([ctx[0]], device), *args, kv, ctx[0], mq, mk,
+                             SCALE, want_lse=True)
+    torch.cuda.synchronize()
+    assert torch.equal(out, again), "not deterministic"
+    assert torch.equal(oa, out) and torch.equal(la, lse), "append part of mixed() differs"
+    if fp8:
+        ref, ref_lse = oracle.append_fp8(bits(t.q_append), w.cu_q(), w.ctx_lens, bits(k), bits(v),
+                                         *scales, w.append_table(), SCALE)
+    else:
+        ref, ref_lse = oracle.append(bits(t.q_append), w.cu_q(), w.ctx_lens, bits(k), bits(v),
+                                     w.append_table(), SCALE)
+    assert_attn_close(out.cpu().numpy(), ref, "append line")
+    np.testing.assert_allclose(lse.cpu().numpy(), ref_lse, atol=APPEND_LSE_ATOL, rtol=0)
