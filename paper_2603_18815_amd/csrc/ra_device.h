@@ -124,6 +124,23 @@ __device__ __forceinline__ int clamp_page(int id, int num_pages) {
   return min(max(id, 0), num_pages - 1);
 }
 
+// Largest i in [0, n) with value(i) <= pos, for a non-decreasing value() with
+// value(0) <= pos (0 if there is none); all 64 lanes of a wave call it
+// together (64 probes a round).
+template <typename Value>
+__device__ __forceinline__ int wave_search(int n, int pos, Value value) {
+  const int lane = threadIdx.x & (kWave - 1);
+  int lo = 0, len = n;
+  while (len > 1) {
+    const int step = (len + kWave - 1) / kWave, off = lane * step;
+    const bool le = off < len && value(lo + off) <= pos;
+    const int c = max(__popcll(__ballot(le)) - 1, 0);
+    lo += c * step;
+    len = min(step, len - c * step);
+  }
+  return lo;
+}
+
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 

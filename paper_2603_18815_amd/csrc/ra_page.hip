@@ -16,16 +16,46 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kVPitch = kHeadDim + 8;  // LDS row pitch (elements) of the staged V slots
 
-// One (row, page, KV head) block per workgroup.
-template <bool kFp8, bool kRope>
-__global__ __launch_bounds__(pwrite::kItemThreads) void page_write_kernel(pwrite::WriteArgs a) {
-  const pwrite::WriteItem it = pwrite::write_item(a, blockIdx.x, blockIdx.z);
+// One page and kHeads KV heads (y) per workgroup. kSearch: the pages are items
+// counted by tokens (x, then z), whose row is found by search; otherwise the
+// grid is every row (z) at the longest chunk's pages (x).
+template <bool kFp8, bool kRope, int kHeads, bool kSearch>
+__global__ __launch_bounds__(pwrite::kItemThreads) void page_write_kernel(pwrite::WriteArgs a,
+                                                                          int32_t B) {
+  __shared__ uint16_t sv[kHeads][kPage][pwrite::kVPitch];
+  const pwrite::WriteItem it =
+      kSearch ? pwrite::item_page(a, B, (int)(blockIdx.z * gridDim.x + blockIdx.x))
+              : pwrite::write_item(a, blockIdx.x, blockIdx.z);
   if (!it.active) return;
-  __shared__ uint16_t sv[kPage][pwrite::kVPitch];
-  pwrite::write_phase1<kFp8, kRope>(a, it, blockIdx.y, threadIdx.x, sv);
-  __syncthreads();
-  pwrite::write_phase2<kFp8>(a, it, blockIdx.y, threadIdx.x, sv);
+  pwrite::write_heads<kFp8, kRope, kHeads>(a, it, blockIdx.y * kHeads, threadIdx.x, sv);
 }
+
+template <int kHeads, bool kSearch>
+void launch_write(const pwrite::WriteArgs &a, int32_t B, dim3 grid, hipStream_t stream) {
+  const dim3 block(pwrite::kItemThreads);
+  if (a.fp8 && a.cos_sin)
+    hipLaunchKernelGGL((page_write_kernel<true, true, kHeads, kSearch>), grid, block, 0, stream, a, B);
+  else if (a.cos_sin)
+    hipLaunchKernelGGL((page_write_kernel<false, true, kHeads, kSearch>), grid, block, 0, stream, a, B);
+  else if (a.fp8)
+    hipLaunchKernelGGL((page_write_kernel<true, false, 1, kSearch>), grid, block, 0, stream, a, B);
+  else
+    hipLaunchKernelGGL((page_write_kernel<false, false, 1, kSearch>), grid, block, 0, stream, a, B);
+}
+
+// What the two decisions below turn on, measured (kernel time, GB/s of what is
+// read and written; 8 KV heads): a page write moves 5.8 to 6.1 TB/s either way
+// when its rows are alike.
+// - 32 chunks of 64..2,048 tokens: 46.1 us with the full grid (2.0 workgroups
+//   per page in use), 48.5 us by search; 54 single tokens and 10 chunks of
+//   128..4,096: 44 us with the full grid (10 per page), 23.3 us by search. The
+//   grid is searched once it would be over four times the items.
+// - Rotated keys: four heads of a page share the cosines and sines, 54 -> 47 us
+//   for 32 chunks of 64..2,048 tokens; one head per workgroup otherwise and for
+//   small calls (64 single tokens: 3.9 us with one head, 5.0 us with four).
+constexpr int kFullGrid = 4;
+constexpr int kRopeHeads = 4;
+constexpr int64_t kRopeUnits = 8192;   // (page, head) units from which rotated writes share them
 
 __global__ __launch_bounds__(kThreads) void page_gather_kernel(
     const uint16_t *__restrict__ k_pool, const uint16_t *__restrict__ v_pool,
@@ -97,19 +127,26 @@ hipError_t launch_page_write(const uint16_t *k_new, const uint16_t *v_new, const
                              const int32_t *start_pos, const PagedKV &kv, int32_t B,
                              int32_t total_new, int32_t max_new, int32_t max_pos,
                              hipStream_t stream, const float *cos_sin, int32_t rope_rows) {
-  // A run of n tokens touches at most (n - 1) / 16 + 2 pages.
-  const dim3 grid((unsigned)(((int64_t)max_new + kPage - 1) / kPage + 1), kv.hkv, B);
+  // a run of n tokens touches at most (n - 1) / 16 + 2 pages
+  const int64_t per_row = ((int64_t)max_new + kPage - 1) / kPage + 1;
+  const int64_t counted = pwrite::write_items(B, total_new), row = 1 << 22;   // grid x limit
+  const bool search = per_row * B > kFullGrid * counted;
+  const int64_t items = search ? counted : per_row * B;
+  const int heads = cos_sin && items * kv.hkv >= kRopeUnits ? kRopeHeads : 1;
+  const unsigned groups = (kv.hkv + heads - 1) / heads;
+  const dim3 grid = search ? dim3((unsigned)(items < row ? items : row), groups,
+                                  (unsigned)((items + row - 1) / row))
+                           : dim3((unsigned)per_row, groups, B);
   const pwrite::WriteArgs a = pwrite::write_args(k_new, v_new, cu_new, start_pos, kv, total_new,
                                                  max_new, max_pos, cos_sin, rope_rows);
-  const dim3 block(pwrite::kItemThreads);
-  if (kv.fp8 && cos_sin)
-    hipLaunchKernelGGL((page_write_kernel<true, true>), grid, block, 0, stream, a);
-  else if (kv.fp8)
-    hipLaunchKernelGGL((page_write_kernel<true, false>), grid, block, 0, stream, a);
-  else if (cos_sin)
-    hipLaunchKernelGGL((page_write_kernel<false, true>), grid, block, 0, stream, a);
+  if (search && heads > 1)
+    launch_write<kRopeHeads, true>(a, B, grid, stream);
+  else if (search)
+    launch_write<1, true>(a, B, grid, stream);
+  else if (heads > 1)
+    launch_write<kRopeHeads, false>(a, B, grid, stream);
   else
-    hipLaunchKernelGGL((page_write_kernel<false, false>), grid, block, 0, stream, a);
+    launch_write<1, false>(a, B, grid, stream);
   return hipGetLastError();
 }
 

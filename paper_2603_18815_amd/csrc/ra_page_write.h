@@ -1,6 +1,11 @@
-// Page write of one (row, page, KV head) block of K/V, shared by the page
-// write kernel and the planned append launch that writes the chunks itself.
-// 256 threads move one block: K rows go to the token-major page 16 source
+// Page write of the K/V of one (row, page) and a few KV heads, shared by the
+// page write kernel and the planned append launch that writes the chunks
+// itself. The page items of a call can be counted from its rows and tokens
+// alone (write_items), each finding its row by a search over cu_new, so that a
+// batch of decode rows with a few long chunks among them launches no more than
+// its tokens need (a grid of every row at the longest chunk's pages is then
+// nine tenths empty).
+// 256 threads move one (page, head) block: K rows go to the token-major page 16 source
 // bytes per lane; V tokens go through LDS so that the dim-major page is
 // written in 8- or 16-byte pieces per lane as well (partial pages: element
 // stores on the touched slots only).
@@ -67,6 +72,17 @@ struct WriteItem {
   int cu0, s, pg, lo, hi, id;
 };
 
+// First page item of row b: a row of n tokens touches at most n / 16 + 2 pages,
+// and floor((x + n) / 16) - floor(x / 16) >= floor(n / 16).
+__device__ __forceinline__ int row_item(const WriteArgs &a, int b) {
+  return min(max(a.cu_new[b], 0), a.total_new) / kPage + 2 * b;
+}
+
+// Page items of a call.
+inline int64_t write_items(int32_t B, int32_t total_new) {
+  return (int64_t)total_new / kPage + 2 * (int64_t)B;
+}
+
 // Row extent clamped so that no access leaves the caller's arrays.
 __device__ __forceinline__ WriteItem write_item(const WriteArgs &a, int chunk, int b) {
   WriteItem it;
@@ -85,33 +101,50 @@ __device__ __forceinline__ WriteItem write_item(const WriteArgs &a, int chunk, i
   return it;
 }
 
-// Phase 1 (thread t of 256): K rows to the page, V tokens into LDS.
-template <bool kFp8, bool kRope = false>
-__device__ __forceinline__ void write_phase1(const WriteArgs &a, const WriteItem &it, int g,
-                                             int t, uint16_t (*sv)[kVPitch]) {
+// The page of item `item`; called by whole waves.
+__device__ __forceinline__ WriteItem item_page(const WriteArgs &a, int B, int item) {
+  const int b = wave_search(B, item, [&](int i) { return row_item(a, i); });
+  return write_item(a, item - row_item(a, b), b);
+}
+
+// Phase 1 (thread t of 256): K rows to the page, V tokens into LDS, heads
+// g0 .. g0 + kHeads - 1 with all their loads in flight together.
+template <bool kFp8, bool kRope, int kHeads>
+__device__ __forceinline__ void write_phase1(const WriteArgs &a, const WriteItem &it, int g0, int t,
+                                             uint16_t (*sv)[kPage][kVPitch]) {
   const int slot = t >> 4, ch = t & 15;            // token slot, 8-element chunk
   const int pos = it.pg * kPage + slot;
-  if (pos >= it.lo && pos < it.hi) {
-    const size_t row = ((size_t)(it.cu0 + pos - it.s) * a.hkv + g) * kHeadDim;
-    const size_t src = row + ch * 8;
-    const size_t dst = (((size_t)it.id * a.hkv + g) * kPage + slot) * kHeadDim + ch * 8;
-    u32x4 k = load_u32x4(a.k_new + src);
-    if constexpr (kRope) {
-      // this chunk's dims 8 ch + 0..7 pair with chunk ch ^ 8; frequency index
-      // 8 (ch % 8) + 0..7
-      const u32x4 partner = load_u32x4(a.k_new + row + (ch ^ 8) * 8);
-      const float *cs = a.cos_sin + (size_t)min(pos, a.rope_rows - 1) * kHeadDim + (ch & 7) * 8;
-      const f32x8 c = *reinterpret_cast<const f32x8 *>(cs);
-      const f32x8 sn = *reinterpret_cast<const f32x8 *>(cs + kHeadDim / 2);
-      k = __builtin_bit_cast(u32x4, rope8(__builtin_bit_cast(bf16x8, k),
-                                          __builtin_bit_cast(bf16x8, partner), c, sn, ch >= 8));
-    }
+  if (pos < it.lo || pos >= it.hi) return;
+  const size_t row0 = ((size_t)(it.cu0 + pos - it.s) * a.hkv + g0) * kHeadDim;
+  u32x4 k[kHeads], partner[kHeads], v[kHeads];
+#pragma unroll
+  for (int h = 0; h < kHeads; ++h) {
+    if (g0 + h >= a.hkv) break;
+    const uint16_t *src = a.k_new + row0 + h * kHeadDim;
+    k[h] = load_u32x4(src + ch * 8);
+    // rope: this chunk's dims 8 ch + 0..7 pair with chunk ch ^ 8
+    if constexpr (kRope) partner[h] = load_u32x4(src + (ch ^ 8) * 8);
+    v[h] = load_u32x4(a.v_new + row0 + h * kHeadDim + ch * 8);
+  }
+  f32x8 c{}, sn{};
+  if constexpr (kRope) {   // frequency index 8 (ch % 8) + 0..7, the same for every head
+    const float *cs = a.cos_sin + (size_t)min(pos, a.rope_rows - 1) * kHeadDim + (ch & 7) * 8;
+    c = *reinterpret_cast<const f32x8 *>(cs);
+    sn = *reinterpret_cast<const f32x8 *>(cs + kHeadDim / 2);
+  }
+#pragma unroll
+  for (int h = 0; h < kHeads; ++h) {
+    if (g0 + h >= a.hkv) break;
+    const size_t dst = (((size_t)it.id * a.hkv + g0 + h) * kPage + slot) * kHeadDim + ch * 8;
+    if constexpr (kRope)
+      k[h] = __builtin_bit_cast(u32x4, rope8(__builtin_bit_cast(bf16x8, k[h]),
+                                             __builtin_bit_cast(bf16x8, partner[h]), c, sn, ch >= 8));
     if constexpr (kFp8)
       *reinterpret_cast<u32x2 *>(reinterpret_cast<uint8_t *>(a.k_pool) + dst) =
-          quantize8(k, a.k_inv);
+          quantize8(k[h], a.k_inv);
     else
-      store_u32x4(a.k_pool + dst, k);
-    *reinterpret_cast<u32x4 *>(&sv[slot][ch * 8]) = load_u32x4(a.v_new + src);
+      store_u32x4(a.k_pool + dst, k[h]);
+    *reinterpret_cast<u32x4 *>(&sv[h][slot][ch * 8]) = v[h];
   }
 }
 
@@ -148,6 +181,19 @@ __device__ __forceinline__ void write_phase2(const WriteArgs &a, const WriteItem
         if (p0 + e >= it.lo && p0 + e < it.hi) dst[e] = sv[s0 + e][d];
     }
   }
+}
+
+// One page and kHeads heads by 256 threads; every thread of the workgroup calls
+// it (an inactive item only passes the barrier).
+template <bool kFp8, bool kRope, int kHeads>
+__device__ __forceinline__ void write_heads(const WriteArgs &a, const WriteItem &it, int g0, int t,
+                                            uint16_t (*sv)[kPage][kVPitch]) {
+  if (it.active) write_phase1<kFp8, kRope, kHeads>(a, it, g0, t, sv);
+  __syncthreads();
+  if (!it.active) return;
+#pragma unroll
+  for (int h = 0; h < kHeads; ++h)
+    if (g0 + h < a.hkv) write_phase2<kFp8>(a, it, g0 + h, t, sv[h]);
 }
 
 }  // namespace pwrite

@@ -122,21 +122,6 @@ __device__ int block_exclusive_scan(int v, int *s, int *total) {
   return before + incl - v;
 }
 
-// Largest i in [0, n) with start[i] <= pos, for non-decreasing start with
-// start[0] <= pos; all 64 lanes of a wave call it together (64 probes a round).
-__device__ __forceinline__ int wave_search(const int32_t *start, int n, int pos) {
-  const int lane = threadIdx.x & (kWave - 1);
-  int lo = 0, len = n;
-  while (len > 1) {
-    const int step = (len + kWave - 1) / kWave, off = lane * step;
-    const bool le = off < len && start[lo + off] <= pos;
-    const int c = __popcll(__ballot(le)) - 1;   // lane 0 always holds
-    lo += c * step;
-    len = min(step, len - c * step);
-  }
-  return lo;
-}
-
 // KV heads g = q, q + 8, ... below hkv go to queue q.
 __device__ __forceinline__ int heads_of_queue(int hkv, int q) {
   return q < hkv ? (hkv - 1 - q) / kQueues + 1 : 0;
@@ -156,41 +141,30 @@ __device__ __forceinline__ int64_t row_blocks(const atile::AppendArgs &ap, const
   return sum;
 }
 
-// Workgroup 0 plans. With the page write fused in (write_chunks > 0), every
-// other workgroup writes four (row, page, KV head) blocks of the chunks' K/V
-// meanwhile; the attention kernel after this one reads them from the pool.
+// Workgroup 0 plans. With the page write fused in, every other workgroup writes
+// four (page, kFusedHeads KV heads) units of the chunks' K/V meanwhile; the attention kernel after this one
+// reads them from the pool.
+constexpr int kFusedHeads = 2;   // KV heads of a write unit here (LDS for 2 workgroups per CU)
 __global__ __launch_bounds__(kPlanThreads) void mixed_plan_kernel(MixedArgs m, pwrite::WriteArgs w,
-                                                                  int32_t write_chunks) {
+                                                                  int64_t write_units) {
   if (blockIdx.x > 0) {
     constexpr int kPer = kPlanThreads / pwrite::kItemThreads;
-    __shared__ uint16_t sv[kPer][kPage][pwrite::kVPitch];
+    __shared__ uint16_t sv[kPer][kFusedHeads][kPage][pwrite::kVPitch];
     const int part = threadIdx.x / pwrite::kItemThreads, t = threadIdx.x % pwrite::kItemThreads;
-    const int64_t item = (int64_t)(blockIdx.x - 1) * kPer + part;   // (row, head, page)
+    const int64_t unit = (int64_t)(blockIdx.x - 1) * kPer + part;
+    const int groups = (w.hkv + kFusedHeads - 1) / kFusedHeads;
+    const int item = (int)(unit / groups), g0 = (int)(unit - (int64_t)item * groups) * kFusedHeads;
     pwrite::WriteItem it;
     it.active = false;
-    int g = 0;
-    if (item < (int64_t)m.B_append * w.hkv * write_chunks) {
-      const int64_t bg = item / write_chunks;
-      g = (int)(bg % w.hkv);
-      it = pwrite::write_item(w, (int)(item % write_chunks), (int)(bg / w.hkv));
-    }
-    if (it.active) {
-      if (w.fp8 && w.cos_sin)
-        pwrite::write_phase1<true, true>(w, it, g, t, sv[part]);
-      else if (w.fp8)
-        pwrite::write_phase1<true, false>(w, it, g, t, sv[part]);
-      else if (w.cos_sin)
-        pwrite::write_phase1<false, true>(w, it, g, t, sv[part]);
-      else
-        pwrite::write_phase1<false, false>(w, it, g, t, sv[part]);
-    }
-    __syncthreads();
-    if (it.active) {
-      if (w.fp8)
-        pwrite::write_phase2<true>(w, it, g, t, sv[part]);
-      else
-        pwrite::write_phase2<false>(w, it, g, t, sv[part]);
-    }
+    if (unit < write_units) it = pwrite::item_page(w, m.B_append, item);
+    if (w.fp8 && w.cos_sin)
+      pwrite::write_heads<true, true, kFusedHeads>(w, it, g0, t, sv[part]);
+    else if (w.fp8)
+      pwrite::write_heads<true, false, kFusedHeads>(w, it, g0, t, sv[part]);
+    else if (w.cos_sin)
+      pwrite::write_heads<false, true, kFusedHeads>(w, it, g0, t, sv[part]);
+    else
+      pwrite::write_heads<false, false, kFusedHeads>(w, it, g0, t, sv[part]);
     return;
   }
   __shared__ int count[kCostBuckets];   // rows per key-block count, then write cursors
@@ -394,7 +368,8 @@ __global__ __launch_bounds__(kMixThreads, 1) void mixed_kernel(MixedArgs args) {
       const int64_t line = (int64_t)s_header[kHead] * m.ap.hkv, share = s_header[kShare];
       st.pos = (int)(w * share);
       st.end = (int)min(line, (w + 1) * share);
-      st.tile = wave_search(m.tile_start, s_header[kTiles], st.pos % s_header[kHead]);
+      st.tile = wave_search(s_header[kTiles], st.pos % s_header[kHead],
+                            [&](int i) { return m.tile_start[i]; });
     }
     if (threadIdx.x == 0) s_state[0] = st;
   }
@@ -444,7 +419,7 @@ __global__ __launch_bounds__(kMixThreads, 1) void mixed_kernel(MixedArgs args) {
       }
     }
     if (decode) {
-      const int row = wave_search(m.split_start, m.de.B, index);
+      const int row = wave_search(m.de.B, index, [&](int i) { return m.split_start[i]; });
       dsplit::decode_split<kDecodeTiles, false, kMixWaves, kFp8>(
           m.de, head, index - uniform(m.split_start[row]), row, lds.de);
       if (threadIdx.x == 0)
@@ -626,11 +601,14 @@ hipError_t launch_mixed(const uint16_t *q_decode, const PagedKV &kv_decode,
   // the fused page write (append rows only): the chunks' tokens at ctx_lens
   const pwrite::WriteArgs w = pwrite::write_args(k_new, v_new, cu_q, ctx_lens, kv_append, total_q,
                                                  max_q_len, max_kv_len_append, cos_sin, rope_rows);
-  const int32_t write_chunks = k_new ? (int32_t)(((int64_t)max_q_len + kPage - 1) / kPage + 1) : 0;
-  const int64_t write_blocks =
-      ((int64_t)B_append * kv_append.hkv * write_chunks + 3) / (kPlanThreads / pwrite::kItemThreads);
+  const int64_t write_units =
+      k_new ? pwrite::write_items(B_append, total_q) *
+                  ((kv_append.hkv + kFusedHeads - 1) / kFusedHeads)
+            : 0;
+  constexpr int64_t kUnitsPer = kPlanThreads / pwrite::kItemThreads;
+  const int64_t write_blocks = (write_units + kUnitsPer - 1) / kUnitsPer;
   hipLaunchKernelGGL(mixed_plan_kernel, dim3((unsigned)(1 + write_blocks)), dim3(kPlanThreads), 0,
-                     stream, m, w, write_chunks);
+                     stream, m, w, write_units);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   // One workgroup per CU: the kernel's registers allow one 8-wave
