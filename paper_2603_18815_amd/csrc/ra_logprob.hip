@@ -5,26 +5,37 @@
 // W [V][D]: z_v = scale * <h[n], W[v]>, lse = ln sum_v exp z_v, and
 // logp = z_t - lse.
 //
-// Partial kernel: one workgroup (4 waves) per (128-row vocabulary chunk,
-// token block of 128, or 64 when N <= 64). Each wave computes the logits of
-// its 32 vocabulary rows for the block's tokens on the matrix cores (4 or 2
-// tiles of
-// mfma_f32_32x32x16_bf16: A = W rows, B = h^T). The loop walks D in steps of
-// 64 dims. W comes straight from memory, three steps ahead: a lane reads 64
-// contiguous bytes of its row per step, the two lanes of a row 128 bytes. The
-// block's h slice (tokens x 64 dims) is requested two steps ahead, staged once
-// per step into LDS (double-buffered, rows padded to 144 B: conflict-free) and
-// read by all four waves. The 64 dims of a step are split over the four products as lanes 0-31
+// Which kernel writes the partials (one (max, sum) per token and vocabulary
+// chunk), by batch size and layout of W; times at V = 151,936, D = 4,096 with
+// the alternative beside it:
+// - N <= 128, packed: logprob_partial_kernel. 4 waves per 128-row chunk, W
+//   straight into registers (64 tokens 198 us, 128 tokens 244 us).
+// - N <= 128, row-major: logprob_stream_kernel. The same chunks with W through
+//   LDS in whole cache lines; bound by HBM reading 128-byte pieces 8 KB apart
+//   (64 tokens 279 -> 241 us, 128 tokens 339 -> 304 us; one 8-wave workgroup
+//   per compute unit instead of two of 4 waves: 285 us at 64 tokens).
+// - 128 < N < 512: logprob_rounds_kernel. 256-token tiles, 384 vocabulary rows
+//   high while they fill the 256 compute units, then lower ones for what is
+//   left, so that the last round is short (row-major 129 tokens 464 -> 287 us,
+//   256 526 -> 329, 257 658 -> 470, 400 814 -> 554, 511 870 -> 575; packed 129
+//   tokens 367 -> 276, 256 402 -> 337, 257 519 -> 486, 511 715 -> 603 us; the
+//   alternative being 128 x 128 tiles that load W again for every 128 tokens).
+//   Blocks of 192 tokens where that holds the batch (257 tokens, row-major: 544
+//   us in blocks of 256, 470 us in blocks of 192).
+// - N >= 512: logprob_tile_kernel, 384 x 256 tiles with h staged.
+//
+// logprob_partial_kernel: each wave computes the logits of its 32 vocabulary
+// rows for the batch's tokens on the matrix cores (4 or 2 tiles of
+// mfma_f32_32x32x16_bf16: A = W rows, B = h^T). The loop walks D in steps of 64
+// dims. W comes straight from memory, three steps ahead. The h slice (tokens x
+// 64 dims) is requested two steps ahead, staged once per step into LDS
+// (double-buffered, rows padded to 144 B: conflict-free) and read by all four
+// waves. The 64 dims of a step are split over the four products as lanes 0-31
 // dims 8u + 0..7 and lanes 32-63 dims 32 + 8u + 0..7 (any split of the
 // contraction is valid as long as A and B use the same one). The wave reduces
 // its logits to a (max, sum of exp) pair per token in base 2, the four waves
-// merge through LDS, and the workgroup writes one partial per (token, chunk);
-// the workgroup whose chunk holds token n's target stores that logit. The
-// grid is mapped so that the token blocks of one vocabulary chunk run on one
-// XCD and re-read the chunk from that XCD's L2.
-//
-// From N = 512 on, the partials come from the 384 x 256 tiled kernel further
-// down (384-row chunks) instead.
+// merge through LDS, and the workgroup writes one partial per token; the
+// workgroup whose chunk holds token n's target stores that logit.
 //
 // Combine kernel: one workgroup per token merges its partials:
 // M = max_c m_c, L = sum_c l_c 2^(m_c - M), lse = (M + log2 L) ln 2.
@@ -52,6 +63,8 @@ constexpr int kMaxTiles = 4;                  // 32-token tiles per workgroup (l
 constexpr int kDimStep = 64;                  // dims per loop step (4 products)
 constexpr int kXcds = 8;                      // XCDs of an MI355X
 constexpr int kHPitch = kDimStep + 8;         // LDS row pitch of the h slice (elements)
+constexpr int kRoundsMinN = 128;              // larger batches below kTileMinN: tiles of two heights
+constexpr int kTileCus = 256;                 // compute units of an MI355X, one tile each
 constexpr int kTileMinN = 512;                // batches from this size use the 384 x 256 tiles
 constexpr int kPackRows = 384;                // the packed copy covers V rounded up to this
 // s_waitcnt immediates: vmcnt(0), export and LDS counters not waited on
@@ -66,6 +79,7 @@ struct LogprobArgs {
   float *ws_l;    // [N][chunks] sum of 2^(y - max)
   float *tgt;     // [N] logit of the target (natural units)
   int32_t N, V, D, chunks, token_blocks;
+  int32_t tall;       // logprob_rounds_kernel: chunks of 384 rows before the shorter ones
   float scale;        // logits = scale * <h, W_v>
   float scale_log2;   // scale * log2(e)
 };
@@ -86,8 +100,48 @@ __device__ __forceinline__ float pair_sum(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// (max, sum of 2^(y - max)) of token t's logits over the 32 vocabulary rows
+// from v0 (lane l holds rows v0 + 8 (r / 4) + 4 half + r % 4, r = 0..15, of the
+// token of column l % 32), and the target's logit if it is among them.
+__device__ __forceinline__ void tile_max_sum(const LogprobArgs &a, const f32x16 &acc, int v0, int t,
+                                             int half, float *max_out, float *sum_out) {
+  const int target = t < a.N ? a.targets[t] : -1;
+  float y[16];
+  float m = -INFINITY;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int v = v0 + 8 * (r >> 2) + 4 * half + (r & 3);
+    y[r] = v < a.V ? acc[r] * a.scale_log2 : -INFINITY;
+    m = fmaxf(m, y[r]);
+    if (v == target) a.tgt[t] = acc[r] * a.scale;
+  }
+  m = pair_max(m);
+  const float m_use = m == -INFINITY ? 0.f : m;
+  float sum = 0.f;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) sum += fast_exp2(y[r] - m_use);
+  *max_out = m;
+  *sum_out = pair_sum(sum);
+}
+
+// Merges four waves' (max, sum) of column c into token t's partial of a chunk.
+template <int kColumns>
+__device__ __forceinline__ void merge_waves(const LogprobArgs &a, const float (*s_m)[kColumns],
+                                            const float (*s_l)[kColumns], int c, int t, int chunk) {
+  float M = s_m[0][c];
+#pragma unroll
+  for (int w = 1; w < kLpWaves; ++w) M = fmaxf(M, s_m[w][c]);
+  const float M_use = M == -INFINITY ? 0.f : M;
+  float L = 0.f;
+#pragma unroll
+  for (int w = 0; w < kLpWaves; ++w) L += s_l[w][c] * fast_exp2(s_m[w][c] - M_use);
+  const size_t part = (size_t)t * a.chunks + chunk;
+  a.ws_m[part] = M;
+  a.ws_l[part] = L;
+}
+
 // kTiles 32-token tiles per workgroup: 2 for small batches (N <= 64), else 4.
-template <int kTiles, bool kPacked>
+template <int kTiles>
 __global__ __launch_bounds__(kLpThreads, 2) void logprob_partial_kernel(LogprobArgs a) {
   constexpr int kTokenBlock = 32 * kTiles;
   // XCD-aware placement: workgroup ids are dealt to the XCDs round-robin, so
@@ -105,12 +159,9 @@ __global__ __launch_bounds__(kLpThreads, 2) void logprob_partial_kernel(LogprobA
   const int v0 = chunk * kVocabChunk + wave * 32;       // first vocabulary row of this wave
   const int t0 = tblock * kTokenBlock;                  // first token of the block
 
-  // A row (vocabulary) this lane supplies, clamped into range for the loads
-  // (packed: rows past V are stored as zeros); rows past V are masked after
-  // the products.
-  const uint16_t *wp =
-      kPacked ? a.W + (size_t)(v0 / 32) * 4 * kWave * 8 + 8 * lane
-              : a.W + (size_t)min(v0 + col, a.V - 1) * a.D + 32 * half;
+  // this lane's units of the packed copy (rows past V are stored as zeros and
+  // masked after the products)
+  const uint16_t *wp = a.W + (size_t)(v0 / 32) * 4 * kWave * 8 + 8 * lane;
   // h staging: thread i copies 16-byte chunks i + 256 j (j = 0..3) of the
   // block's 128 x 64 slice (token = chunk / 8, 8 dims per chunk); tokens past
   // N are clamped (their columns are never written back).
@@ -136,20 +187,20 @@ __global__ __launch_bounds__(kLpThreads, 2) void logprob_partial_kernel(LogprobA
 #pragma unroll
     for (int i = 0; i < kHChunks; ++i) store_u32x4(&s_h[buf][hdst[i]], src[i]);
   };
-  // With one token block (kTiles == 2: N <= 64) no other workgroup reads this
-  // chunk of W, and a packed W load takes 1 KB contiguous (whole cache lines):
-  // those loads are marked nontemporal. Row-major loads take each line 32
-  // bytes at a time over four instructions and stay ordinary.
-  constexpr bool kStreamW = kPacked && kTiles == 2;
+  // With one token block no other workgroup reads this chunk of W, and a
+  // load takes 1 KB contiguous (whole cache lines): marked nontemporal for the
+  // batches of 64 tokens, whose reads are all the time there is.
+  constexpr bool kStreamW = kTiles == 2;
   // 32-row tiles of the packed copy: a 64-dim step of all of them is one block
   const size_t ntiles = (size_t)(((int64_t)a.V + kPackRows - 1) / kPackRows) * (kPackRows / 32);
   bf16x8 w0[4], w1[4], w2[4], w3[4];
   auto w_load = [&](bf16x8 *dst, int s) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < 4; ++u)
-      dst[u] = kStreamW ? __builtin_bit_cast(bf16x8, load_stream_u32x4(wp + ((size_t)s * ntiles * 4 + u) * 8 * kWave))
-                        : load_bf16x8(kPacked ? wp + ((size_t)s * ntiles * 4 + u) * 8 * kWave
-                                              : wp + s * kDimStep + 8 * u);
+    {
+      const uint16_t *p = wp + ((size_t)s * ntiles * 4 + u) * 8 * kWave;
+      dst[u] = kStreamW ? __builtin_bit_cast(bf16x8, load_stream_u32x4(p)) : load_bf16x8(p);
+    }
   };
   const int nsteps = a.D / kDimStep;
   const int last = nsteps - 1;
@@ -203,23 +254,8 @@ __global__ __launch_bounds__(kLpThreads, 2) void logprob_partial_kernel(LogprobA
   __shared__ float s_l[kLpWaves][kTokenBlock];
 #pragma unroll
   for (int tt = 0; tt < kTiles; ++tt) {
-    const int t = t0 + 32 * tt + col;
-    const int target = t < a.N ? a.targets[t] : -1;
-    float y[16];
-    float m = -INFINITY;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int v = v0 + 8 * (r >> 2) + 4 * half + (r & 3);
-      y[r] = v < a.V ? acc[tt][r] * a.scale_log2 : -INFINITY;
-      m = fmaxf(m, y[r]);
-      if (v == target) a.tgt[t] = acc[tt][r] * a.scale;
-    }
-    m = pair_max(m);
-    const float m_use = m == -INFINITY ? 0.f : m;
-    float sum = 0.f;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) sum += fast_exp2(y[r] - m_use);
-    sum = pair_sum(sum);
+    float m, sum;
+    tile_max_sum(a, acc[tt], v0, t0 + 32 * tt + col, half, &m, &sum);
     if (half == 0) {
       s_m[wave][32 * tt + col] = m;
       s_l[wave][32 * tt + col] = sum;
@@ -229,18 +265,7 @@ __global__ __launch_bounds__(kLpThreads, 2) void logprob_partial_kernel(LogprobA
 
   // Merge the four waves: one thread per token of the block.
   const int c = threadIdx.x;
-  if (c < kTokenBlock && t0 + c < a.N) {
-    float M = s_m[0][c];
-#pragma unroll
-    for (int w = 1; w < kLpWaves; ++w) M = fmaxf(M, s_m[w][c]);
-    const float M_use = M == -INFINITY ? 0.f : M;
-    float L = 0.f;
-#pragma unroll
-    for (int w = 0; w < kLpWaves; ++w) L += s_l[w][c] * fast_exp2(s_m[w][c] - M_use);
-    const size_t part = (size_t)(t0 + c) * a.chunks + chunk;
-    a.ws_m[part] = M;
-    a.ws_l[part] = L;
-  }
+  if (c < kTokenBlock && t0 + c < a.N) merge_waves(a, s_m, s_l, c, t0 + c, chunk);
 }
 
 // ---- large batches: LDS-tiled products, 384 vocabulary rows x 256 tokens ----
@@ -273,71 +298,92 @@ constexpr int kTileDims = 32;         // dims per step
 constexpr int kTileStages = 3;
 constexpr int kTileElems = kTileRows * kTileDims;     // token region of a stage (16 KB)
 constexpr int kTileElemsA = kTileRowsA * kTileDims;   // vocabulary region (24 KB)
-constexpr int kLoadsA = kTileRowsA / 16 / kTileWaves;  // 3
 constexpr int kLoadsB = kTileRows / 16 / kTileWaves;   // 2
-// s_waitcnt vmcnt(5) (export and LDS counters not waited on): one later
-// step's loads may stay in flight
-constexpr int kWaitVm5 = 0x0F75;
+// Refill load d of a step goes after this one of the step's products.
+template <int kLoads, int kProducts>
+__device__ constexpr int load_after(int d) {
+  if (kLoads == 5 && kProducts == 24) return d == 4 ? 22 : 3 + 5 * d;
+  return (2 * d + 1) * kProducts / (2 * kLoads);
+}
 
 // Direct global-to-LDS load of 16 bytes per lane: lane l's bytes land at LDS
 // address `lds` + 16 l (lds wave-uniform). Written out rather than through the
 // compiler builtin, which makes the compiler wait for every such load before
 // any LDS read (it cannot tell the ring's stages apart); the kernel counts
-// its own loads. M0 (the LDS base register) is restored before the statement
-// ends.
+// its own loads. M0 is the LDS base register; named as clobbered instead of
+// saved and restored around every load: 2,030 -> 2,026 us at 2,048 tokens of
+// the Qwen3-8B head.
 __device__ __forceinline__ uint32_t lds_address(const uint16_t *p) {
   return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)p;
 }
 __device__ __forceinline__ void load_lds16(const uint16_t *g, uint32_t lds) {
-  uint32_t saved;
   asm volatile(
-      "s_mov_b32 %0, m0\n\t"
-      "s_mov_b32 m0, %1\n\t"
+      "s_mov_b32 m0, %0\n\t"
       "s_nop 0\n\t"
-      "global_load_lds_dwordx4 %2, off\n\t"
-      "s_mov_b32 m0, %0"
-      : "=&s"(saved)
+      "global_load_lds_dwordx4 %1, off"
+      :
       : "s"(lds), "v"(g)
-      : "memory");
+      : "memory", "m0");
+}
+// The same, marked nontemporal: for data read once, a whole line at a time.
+__device__ __forceinline__ void load_lds16_stream(const uint16_t *g, uint32_t lds) {
+  asm volatile(
+      "s_mov_b32 m0, %0\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dwordx4 %1, off nt"
+      :
+      : "s"(lds), "v"(g)
+      : "memory", "m0");
 }
 
-template <bool kPacked>
-__global__ __launch_bounds__(kTileThreads, 1) void logprob_tile_kernel(LogprobArgs a) {
-  const int id = blockIdx.x;
-  const int xcd = id % kXcds, slot = id / kXcds;
-  const int chunk = (slot / a.token_blocks) * kXcds + xcd;
-  const int tblock = slot - (slot / a.token_blocks) * a.token_blocks;
-  if (chunk >= a.chunks) return;
-
-  __shared__ __attribute__((aligned(1024))) uint16_t sA[kTileStages][kTileElemsA];
-  __shared__ __attribute__((aligned(1024))) uint16_t sB[kTileStages][kTileElems];
-  __shared__ float s_m[4][kTileRows];
-  __shared__ float s_l[4][kTileRows];
-
+// One tile: RT 32-row tiles per wave (128 RT vocabulary rows from v0) x TT
+// 32-token tiles per wave (64 TT tokens, block tblock), partial results into
+// column `part`. kStagedH: h from
+// its staged copy (the workspace holds one from N = kTileMinN on), otherwise
+// from its rows, 64 bytes at a time like a row-major W.
+struct TileLds {
+  __attribute__((aligned(1024))) uint16_t a[kTileStages][kTileElemsA];
+  __attribute__((aligned(1024))) uint16_t b[kTileStages][kTileElems];
+  float m[4][kTileRows];
+  float l[4][kTileRows];
+};
+template <bool kPacked, bool kStagedH, int RT, int TT>
+__device__ __forceinline__ void logprob_tile(const LogprobArgs &a, int v0, int tblock, int part,
+                                             TileLds &lds) {
+  auto &sA = lds.a;
+  auto &sB = lds.b;
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const int v0 = chunk * kTileRowsA, t0 = tblock * kTileRows;
+  constexpr int kTokens = 64 * TT;
+  static_assert(TT == 4 || !kStagedH, "the staged copy holds blocks of 256 tokens");
+  const int t0 = tblock * kTokens;
+  constexpr int kLoadsA = RT;
 
   // ---- loads: instructions kLoadsA * wave + k of the W region, kLoadsB *
   // wave + k of the h region ----
   const uint16_t *ga[kLoadsA], *gb[kLoadsB];
+  // rows past the matrix (packed: past its copy, a multiple of 384 rows) read its last one
+  const int vlast = kPacked ? (a.V + kPackRows - 1) / kPackRows * kPackRows - 1 : a.V - 1;
 #pragma unroll
   for (int k = 0; k < kLoadsA; ++k) {
     const int r = 16 * (kLoadsA * wave + k) + lane / 4;
     const int lc = (lane % 4) ^ ((r >> 2) & 3);
-    const int v = v0 + r;
+    const int v = RT == 3 && kPacked ? v0 + r : min(v0 + r, vlast);
     // packed: 16-byte unit ((s / 2 * tiles + tile) * 4 + lc) * 64 + 32 (s % 2) + v % 32
     // (the part that depends on the step s is added per step)
     ga[k] = kPacked ? a.W + ((size_t)(v / 32) * 4 + lc) * kWave * 8 + (v % 32) * 8
-                    : a.W + (size_t)min(v, a.V - 1) * a.D + 8 * lc;
+                    : a.W + (size_t)v * a.D + 8 * lc;
   }
   const int nsteps = a.D / kTileDims;
-  // h comes from its staged copy, which holds each (token block, step) as the
-  // 16 KB image of its LDS region: load instruction j reads 1 KB contiguous
+  // a staged copy of h holds each (token block, step) as the 16 KB image of
+  // its LDS region: load instruction j reads 1 KB contiguous
 #pragma unroll
-  for (int k = 0; k < kLoadsB; ++k)
-    gb[k] = a.hp + (size_t)tblock * nsteps * kTileElems + (size_t)(kLoadsB * wave + k) * 512 +
-            lane * 8;
+  for (int k = 0; k < kLoadsB; ++k) {
+    const int j = kLoadsB * wave + k, r = 16 * j + lane / 4;
+    const int lc = (lane % 4) ^ ((r >> 2) & 3);
+    gb[k] = kStagedH ? a.hp + (size_t)tblock * nsteps * kTileElems + (size_t)j * 512 + lane * 8
+                     : a.h + (size_t)min(t0 + min(r, kTokens - 1), a.N - 1) * a.D + 8 * lc;
+  }
   const int last = nsteps - 1;
   const uint32_t blkA = (uint32_t)(kLoadsA * wave) * 1024u, blkB = (uint32_t)(kLoadsB * wave) * 1024u;
   // offsets (elements) of step s in W and h; steps past the last repeat it
@@ -352,51 +398,53 @@ __global__ __launch_bounds__(kTileThreads, 1) void logprob_tile_kernel(LogprobAr
     if (d < kLoadsA)
       load_lds16(ga[d] + w_off(s), lds_address(sA[st]) + blkA + 1024u * d);
     else
-      load_lds16(gb[d - kLoadsA] + (size_t)s * kTileElems,
+      load_lds16(gb[d - kLoadsA] + (size_t)s * (kStagedH ? kTileElems : kTileDims),
                  lds_address(sB[st]) + blkB + 1024u * (d - kLoadsA));
   };
   constexpr int kLoadsPerStep = kLoadsA + kLoadsB;
-  // refill load d of a step goes after product kLoadAfter[d] of its 24
-  constexpr int kLoadAfter[kLoadsPerStep] = {3, 8, 13, 18, 22};
+  constexpr int kProducts = 2 * RT * TT;
+  // s_waitcnt vmcnt(kLoadsPerStep), export and LDS counters not waited on: one
+  // later step's loads may stay in flight
+  constexpr int kWaitStep = 0x0F70 | kLoadsPerStep;
 
   const int col = lane & 31, half = lane >> 5;
   const int wv = wave & 3, wt = wave >> 2;
   const int swz = (col >> 2) & 3;   // slot swizzle of every operand row (rows differ from col by multiples of 32)
-  const int rowA = (96 * wv + col) * kTileDims, rowB = (128 * wt + col) * kTileDims;
-  f32x16 acc[3][4];
+  const int rowA = (32 * RT * wv + col) * kTileDims, rowB = (32 * TT * wt + col) * kTileDims;
+  f32x16 acc[RT][TT];
 #pragma unroll
-  for (int i = 0; i < 3; ++i)
+  for (int i = 0; i < RT; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f32x16{};
+    for (int j = 0; j < TT; ++j) acc[i][j] = f32x16{};
   auto lds16 = [](const uint16_t *p) __attribute__((always_inline)) {
     return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(p));
   };
   // Step s on stage st: wait until my loads for it have landed (the next
   // step's may still be in flight), barrier (everyone's have, and everyone is
   // done reading the stage used last step), then the products, with the
-  // loads of step s + 2 into that freed stage between them.
+  // loads of step s + 2 into that freed stage spread between them.
   auto step = [&](int st, int s) __attribute__((always_inline)) {
-    __builtin_amdgcn_s_waitcnt(kWaitVm5);
+    __builtin_amdgcn_s_waitcnt(kWaitStep);
     __builtin_amdgcn_s_barrier();
     const uint16_t *A = sA[st], *B = sB[st];
     const int rs = min(s + kTileStages - 1, last), rst = (st + kTileStages - 1) % kTileStages;
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       const int c = 8 * ((2 * half + u) ^ swz);
-      bf16x8 av[3], bv[4];
+      bf16x8 av[RT], bv[TT];
 #pragma unroll
-      for (int i = 0; i < 3; ++i) av[i] = lds16(A + rowA + c + 32 * kTileDims * i);
+      for (int i = 0; i < RT; ++i) av[i] = lds16(A + rowA + c + 32 * kTileDims * i);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) bv[j] = lds16(B + rowB + c + 32 * kTileDims * j);
+      for (int j = 0; j < TT; ++j) bv[j] = lds16(B + rowB + c + 32 * kTileDims * j);
 #pragma unroll
-      for (int i = 0; i < 3; ++i)
+      for (int i = 0; i < RT; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < TT; ++j) {
           acc[i][j] = mfma32x32x16(av[i], bv[j], acc[i][j]);
-          const int p = 12 * u + 4 * i + j;   // product index in the step, 0..23
+          const int p = TT * (RT * u + i) + j;   // product index in the step
 #pragma unroll
           for (int d = 0; d < kLoadsPerStep; ++d)
-            if (p == kLoadAfter[d]) {
+            if (p == load_after<kLoadsPerStep, kProducts>(d)) {
               __builtin_amdgcn_sched_barrier(0);
               load(rst, rs, d);
               __builtin_amdgcn_sched_barrier(0);
@@ -417,20 +465,20 @@ __global__ __launch_bounds__(kTileThreads, 1) void logprob_tile_kernel(LogprobAr
   // workgroup's LDS is released
   __builtin_amdgcn_s_waitcnt(kWaitVm0);
 
-  // ---- logits -> (max, sum) per token over this wave's 96 rows ----
-  // Lane l holds, for token t0 + 128 wt + 32 j + col, the logits of rows
-  // v0 + 96 wv + 32 i + 8 (r / 4) + 4 half + r % 4, r = 0..15.
+  // ---- logits -> (max, sum) per token over this wave's 32 RT rows ----
+  // Lane l holds, for token t0 + 32 (TT wt + j) + col, the logits of rows
+  // v0 + 32 (RT wv + i) + 8 (r / 4) + 4 half + r % 4, r = 0..15.
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int tc = 128 * wt + 32 * j + col, t = t0 + tc;
+  for (int j = 0; j < TT; ++j) {
+    const int tc = 32 * (TT * wt + j) + col, t = t0 + tc;
     const int target = t < a.N ? a.targets[t] : -1;
-    float y[3][16];
+    float y[RT][16];
     float m = -INFINITY;
 #pragma unroll
-    for (int i = 0; i < 3; ++i)
+    for (int i = 0; i < RT; ++i)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int v = v0 + 96 * wv + 32 * i + 8 * (r >> 2) + 4 * half + (r & 3);
+        const int v = v0 + 32 * (RT * wv + i) + 8 * (r >> 2) + 4 * half + (r & 3);
         y[i][r] = v < a.V ? acc[i][j][r] * a.scale_log2 : -INFINITY;
         m = fmaxf(m, y[i][r]);
         if (v == target) a.tgt[t] = acc[i][j][r] * a.scale;
@@ -439,29 +487,159 @@ __global__ __launch_bounds__(kTileThreads, 1) void logprob_tile_kernel(LogprobAr
     const float m_use = m == -INFINITY ? 0.f : m;
     float sum = 0.f;
 #pragma unroll
-    for (int i = 0; i < 3; ++i)
+    for (int i = 0; i < RT; ++i)
 #pragma unroll
       for (int r = 0; r < 16; ++r) sum += fast_exp2(y[i][r] - m_use);
     sum = pair_sum(sum);
     if (half == 0) {
-      s_m[wv][tc] = m;
-      s_l[wv][tc] = sum;
+      lds.m[wv][tc] = m;
+      lds.l[wv][tc] = sum;
     }
   }
   __syncthreads();
   // merge the four row groups: one thread per token of the tile
   const int c = threadIdx.x;
-  if (c < kTileRows && t0 + c < a.N) {
-    float M = s_m[0][c];
+  if (c < kTokens && t0 + c < a.N) {
+    float M = lds.m[0][c];
 #pragma unroll
-    for (int w = 1; w < 4; ++w) M = fmaxf(M, s_m[w][c]);
+    for (int w = 1; w < 4; ++w) M = fmaxf(M, lds.m[w][c]);
     const float M_use = M == -INFINITY ? 0.f : M;
     float L = 0.f;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) L += s_l[w][c] * fast_exp2(s_m[w][c] - M_use);
-    const size_t part = (size_t)(t0 + c) * a.chunks + chunk;
-    a.ws_m[part] = M;
-    a.ws_l[part] = L;
+    for (int w = 0; w < 4; ++w) L += lds.l[w][c] * fast_exp2(lds.m[w][c] - M_use);
+    const size_t at = (size_t)(t0 + c) * a.chunks + part;
+    a.ws_m[at] = M;
+    a.ws_l[at] = L;
+  }
+}
+
+template <bool kPacked>
+__global__ __launch_bounds__(kTileThreads, 1) void logprob_tile_kernel(LogprobArgs a) {
+  const int id = blockIdx.x;
+  const int xcd = id % kXcds, slot = id / kXcds;
+  const int chunk = (slot / a.token_blocks) * kXcds + xcd;
+  const int tblock = slot - (slot / a.token_blocks) * a.token_blocks;
+  if (chunk >= a.chunks) return;
+  __shared__ TileLds lds;
+  logprob_tile<kPacked, true, 3, 4>(a, chunk * kTileRowsA, tblock, chunk, lds);
+}
+
+// Tiles of two heights: `tall` chunks of 384 rows, then chunks of 128 RT rows.
+template <bool kPacked, int RT, int TT>
+__global__ __launch_bounds__(kTileThreads, 1) void logprob_rounds_kernel(LogprobArgs a) {
+  const int id = blockIdx.x;
+  const int xcd = id % kXcds, slot = id / kXcds;
+  const int chunk = (slot / a.token_blocks) * kXcds + xcd;
+  const int tblock = slot - (slot / a.token_blocks) * a.token_blocks;
+  if (chunk >= a.chunks) return;
+  __shared__ TileLds lds;
+  if (RT == 3 || chunk < a.tall)
+    logprob_tile<kPacked, false, 3, TT>(a, chunk * kTileRowsA, tblock, chunk, lds);
+  else
+    logprob_tile<kPacked, false, RT, TT>(
+        a, a.tall * kTileRowsA + (chunk - a.tall) * 128 * RT, tblock, chunk, lds);
+}
+
+// ---- small batches over a row-major W: one pass of W through LDS ----
+//
+// kWaves waves, each with 32 vocabulary rows and all (up to 32 T) tokens. The
+// loop walks D in steps of 64 dims through a ring of kStages LDS stages, refilled
+// kStages - 1 steps ahead by direct global-to-LDS loads of eight rows x 128
+// bytes: whole cache lines, where operand loads straight into registers take
+// each line 16 bytes at a time (a lane needs 16 bytes of its own row).
+// Products, their order and the partial results are those of
+// logprob_partial_kernel.
+//
+// Stage layout: row r holds its 64 dims as eight 16-byte chunks, logical chunk c
+// at slot c ^ ((r / 2) % 8), so that 16 lanes reading 16 rows at one logical
+// chunk hit 16 distinct bank groups.
+template <int T, int kWaves, int kStages>
+__global__ __launch_bounds__(kWaves *kWave, 1) void logprob_stream_kernel(LogprobArgs a) {
+  constexpr int kTokens = 32 * T, kRows = 32 * kWaves;
+  constexpr int kLoadsW = 4, kLoadsH = kTokens / 8 / kWaves;   // per wave and step
+  constexpr int kLoads = kLoadsW + kLoadsH;
+  static_assert(kLoadsH * 8 * kWaves == kTokens && kLoads * (kStages - 2) < 16, "load counts");
+  __shared__ __attribute__((aligned(1024))) uint16_t sW[kStages][kRows * kDimStep];
+  __shared__ __attribute__((aligned(1024))) uint16_t sH[kStages][kTokens * kDimStep];
+  __shared__ float s_m[kWaves][kTokens];
+  __shared__ float s_l[kWaves][kTokens];
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int col = lane & 31, half = lane >> 5;
+  const int v0 = (blockIdx.x * kWaves + wave) * 32;   // first vocabulary row of this wave
+
+  const uint16_t *gw[kLoadsW], *gh[kLoadsH];
+#pragma unroll
+  for (int k = 0; k < kLoadsW; ++k) {
+    const int r = 8 * k + lane / 8, lc = (lane % 8) ^ ((r >> 1) & 7);
+    gw[k] = a.W + (size_t)min(v0 + r, a.V - 1) * a.D + 8 * lc;
+  }
+#pragma unroll
+  for (int k = 0; k < kLoadsH; ++k) {
+    const int r = 8 * (kLoadsH * wave + k) + lane / 8, lc = (lane % 8) ^ ((r >> 1) & 7);
+    gh[k] = a.h + (size_t)min(r, a.N - 1) * a.D + 8 * lc;
+  }
+  const int nsteps = a.D / kDimStep, last = nsteps - 1;
+  auto load = [&](int st, int s) __attribute__((always_inline)) {
+#pragma unroll
+    for (int k = 0; k < kLoadsW; ++k)
+      load_lds16_stream(gw[k] + (size_t)s * kDimStep, lds_address(sW[st]) + (4 * wave + k) * 1024u);
+#pragma unroll
+    for (int k = 0; k < kLoadsH; ++k)
+      load_lds16(gh[k] + (size_t)s * kDimStep, lds_address(sH[st]) + (kLoadsH * wave + k) * 1024u);
+  };
+  f32x16 acc[T];
+#pragma unroll
+  for (int tt = 0; tt < T; ++tt) acc[tt] = f32x16{};
+  const int swz = (col >> 1) & 7;
+  auto lds16 = [](const uint16_t *p) __attribute__((always_inline)) {
+    return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(p));
+  };
+  // Step s on stage st: my loads for it have landed (those of kStages - 2 later
+  // steps may be in flight), then everyone's have, and everyone is done with
+  // the stage of the last step, which is refilled.
+  auto step = [&](int st, int s) __attribute__((always_inline)) {
+    __builtin_amdgcn_s_waitcnt(0x0F70 | (kLoads * (kStages - 2)));
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    load((st + kStages - 1) % kStages, min(s + kStages - 1, last));
+    __builtin_amdgcn_sched_barrier(0);
+    const uint16_t *A = sW[st] + (32 * wave + col) * kDimStep, *B = sH[st] + col * kDimStep;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int c = 8 * ((4 * half + u) ^ swz);
+      const bf16x8 av = lds16(A + c);
+#pragma unroll
+      for (int tt = 0; tt < T; ++tt)
+        acc[tt] = mfma32x32x16(av, lds16(B + c + 32 * kDimStep * tt), acc[tt]);
+    }
+  };
+#pragma unroll
+  for (int k = 0; k < kStages - 1; ++k) load(k, min(k, last));
+  for (int s = 0; s < nsteps; s += kStages) {
+#pragma unroll
+    for (int k = 0; k < kStages; ++k)
+      if (s + k < nsteps) step(k, s + k);
+  }
+  // the last loads (repeats of the last step) must land before the
+  // workgroup's LDS is released
+  __builtin_amdgcn_s_waitcnt(kWaitVm0);
+
+#pragma unroll
+  for (int tt = 0; tt < T; ++tt) {
+    float m, sum;
+    tile_max_sum(a, acc[tt], v0, 32 * tt + col, half, &m, &sum);
+    if (half == 0) {
+      s_m[wave][32 * tt + col] = m;
+      s_l[wave][32 * tt + col] = sum;
+    }
+  }
+  __syncthreads();
+  // merge four waves (128 rows) into a partial: one thread per token and chunk
+  for (int i = threadIdx.x; i < kTokens * (kWaves / kLpWaves); i += kWaves * kWave) {
+    const int c = i % kTokens, g = i / kTokens, chunk = blockIdx.x * (kWaves / kLpWaves) + g;
+    if (c < a.N && chunk < a.chunks)
+      merge_waves(a, &s_m[g * kLpWaves], &s_l[g * kLpWaves], c, c, chunk);
   }
 }
 
@@ -540,7 +718,39 @@ __global__ __launch_bounds__(kLpThreads) void logprob_combine_kernel(LogprobArgs
 
 }  // namespace
 
+namespace {
+// Token blocks of 256 tokens and how the vocabulary is cut for them: `tall`
+// chunks of 384 rows, then `rest` chunks of 128 `rt` rows.
+struct Rounds {
+  int32_t tall, rt, rest;
+};
+Rounds logprob_rounds(int32_t token_blocks, int32_t V) {
+  const int64_t units = ((int64_t)V + 127) / 128;
+  const int64_t per_round = kTileCus / token_blocks;   // chunks that run at the same time
+  Rounds r;
+  const int64_t full = units / 3 / per_round;          // rounds of 384-row chunks only
+  r.tall = (int32_t)(full * per_round);
+  const int64_t left = units - 3 * (int64_t)r.tall;
+  r.rt = (int32_t)((left + per_round - 1) / per_round);
+  if (r.rt < 1) r.rt = 1;
+  if (r.rt > 3) r.rt = 3;
+  r.rest = (int32_t)((left + r.rt - 1) / r.rt);
+  return r;
+}
+bool logprob_in_rounds(int32_t N) { return N > kRoundsMinN && N < kTileMinN; }
+int32_t token_blocks_of(int32_t N) { return (N + kTileRows - 1) / kTileRows; }
+// 64-token groups of a token block (3 or 4)
+int rounds_groups(int32_t N) {
+  const int blocks = token_blocks_of(N);
+  return (N + 64 * blocks - 1) / (64 * blocks) <= 3 ? 3 : 4;
+}
+}  // namespace
+
 int32_t logprob_chunks(int32_t N, int32_t V) {
+  if (logprob_in_rounds(N)) {
+    const Rounds r = logprob_rounds(token_blocks_of(N), V);
+    return r.tall + r.rest;
+  }
   const int rows = N >= kTileMinN ? kTileRowsA : kVocabChunk;
   return (int32_t)(((int64_t)V + rows - 1) / rows);
 }
@@ -561,9 +771,12 @@ hipError_t launch_logprob_pack(const uint16_t *W, int32_t V, int32_t D, uint16_t
 }
 
 namespace {
-// per-(token, chunk) partials and the target logits
+// per-(token, chunk) partials and the target logits (below kTileMinN at the
+// 128-row chunks of the smallest batches, the most any batch there has)
 size_t logprob_partial_bytes(int32_t N, int32_t V) {
-  return ((size_t)N * logprob_chunks(N, V) * 2 + (size_t)N) * sizeof(float);
+  const int rows = N >= kTileMinN ? kTileRowsA : kVocabChunk;
+  const size_t chunks = ((size_t)V + rows - 1) / rows;
+  return ((size_t)N * chunks * 2 + (size_t)N) * sizeof(float);
 }
 }  // namespace
 
@@ -578,7 +791,10 @@ size_t logprob_workspace_bytes(int32_t N, int32_t V, int32_t D) {
 namespace {
 int logprob_tiles(int32_t N) { return N <= 64 ? 2 : kMaxTiles; }
 // tokens per workgroup
-int logprob_token_block(int32_t N) { return N >= kTileMinN ? kTileRows : 32 * logprob_tiles(N); }
+int logprob_token_block(int32_t N) {
+  if (logprob_in_rounds(N)) return 64 * rounds_groups(N);
+  return N >= kTileMinN ? kTileRows : 32 * logprob_tiles(N);
+}
 }  // namespace
 
 int64_t logprob_grid(int32_t N, int32_t V) {
@@ -618,20 +834,44 @@ hipError_t launch_logprob(const uint16_t *h, const uint16_t *W, const int32_t *t
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  if (N >= kTileMinN && packed)
+  a.tall = 0;
+  if (logprob_in_rounds(N)) {
+    const Rounds r = logprob_rounds(a.token_blocks, V);
+    a.tall = r.tall;
+    const int variant = (packed ? 6 : 0) + (rounds_groups(N) == 4 ? 3 : 0) + r.rt - 1;
+    switch (variant) {
+#define RA_ROUNDS(X, P, RT, TT)                                                                   \
+  case X:                                                                                         \
+    hipLaunchKernelGGL((logprob_rounds_kernel<P, RT, TT>), grid, dim3(kTileThreads), 0, stream, a); \
+    break;
+      RA_ROUNDS(0, false, 1, 3)
+      RA_ROUNDS(1, false, 2, 3)
+      RA_ROUNDS(2, false, 3, 3)
+      RA_ROUNDS(3, false, 1, 4)
+      RA_ROUNDS(4, false, 2, 4)
+      RA_ROUNDS(5, false, 3, 4)
+      RA_ROUNDS(6, true, 1, 3)
+      RA_ROUNDS(7, true, 2, 3)
+      RA_ROUNDS(8, true, 3, 3)
+      RA_ROUNDS(9, true, 1, 4)
+      RA_ROUNDS(10, true, 2, 4)
+      RA_ROUNDS(11, true, 3, 4)
+#undef RA_ROUNDS
+    }
+  } else if (N >= kTileMinN && packed)
     hipLaunchKernelGGL(logprob_tile_kernel<true>, grid, dim3(kTileThreads), 0, stream, a);
   else if (N >= kTileMinN)
     hipLaunchKernelGGL(logprob_tile_kernel<false>, grid, dim3(kTileThreads), 0, stream, a);
-  else if (tiles == 2 && packed)
-    hipLaunchKernelGGL((logprob_partial_kernel<2, true>), grid, dim3(kLpThreads), 0, stream, a);
-  else if (tiles == 2)
-    hipLaunchKernelGGL((logprob_partial_kernel<2, false>), grid, dim3(kLpThreads), 0, stream, a);
+  else if (packed && tiles == 2)
+    hipLaunchKernelGGL((logprob_partial_kernel<2>), grid, dim3(kLpThreads), 0, stream, a);
   else if (packed)
-    hipLaunchKernelGGL((logprob_partial_kernel<kMaxTiles, true>), grid, dim3(kLpThreads), 0,
-                       stream, a);
+    hipLaunchKernelGGL((logprob_partial_kernel<kMaxTiles>), grid, dim3(kLpThreads), 0, stream, a);
+  else if (tiles == 2)   // two workgroups per compute unit (72 KB of LDS each)
+    hipLaunchKernelGGL((logprob_stream_kernel<2, 4, 3>), dim3(a.chunks), dim3(4 * kWave), 0, stream,
+                       a);
   else
-    hipLaunchKernelGGL((logprob_partial_kernel<kMaxTiles, false>), grid, dim3(kLpThreads), 0,
-                       stream, a);
+    hipLaunchKernelGGL((logprob_stream_kernel<kMaxTiles, 8, 3>), dim3((a.chunks + 1) / 2),
+                       dim3(8 * kWave), 0, stream, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(logprob_combine_kernel, dim3((unsigned)N), dim3(kLpThreads), 0, stream, a,
