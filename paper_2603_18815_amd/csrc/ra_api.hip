@@ -113,7 +113,7 @@ const char *ra_status_string(int status) {
 size_t rollout_attn_decode_workspace_size(int32_t B, int32_t Hq, int32_t Hkv,
                                           int32_t max_kv_len) {
   if (B <= 0 || Hq <= 0 || Hkv <= 0 || max_kv_len < 0) return 0;
-  return ra::decode_workspace_bytes(B, Hq, ra::decode_plan(B, Hkv, max_kv_len));
+  return ra::decode_workspace_bytes(B, Hq, ra::decode_plan(B, Hkv, max_kv_len, true));
 }
 
 int rollout_attn_decode(const void *q, const ra_paged_kv *kv, const int32_t *kv_lens, int32_t B,
@@ -122,7 +122,7 @@ int rollout_attn_decode(const void *q, const ra_paged_kv *kv, const int32_t *kv_
   const int s = check_decode(q, kv, kv_lens, B, Hq, max_kv_len, scale, out);
   if (s != RA_OK) return s;
   if (B == 0) return RA_OK;
-  const ra::DecodePlan plan = ra::decode_plan(B, kv->num_kv_heads, max_kv_len);
+  const ra::DecodePlan plan = ra::decode_plan(B, kv->num_kv_heads, max_kv_len, true);
   if (!workspace || workspace_bytes < ra::decode_workspace_bytes(B, Hq, plan))
     return RA_ERR_WORKSPACE;
   return hip_status(ra::launch_decode(static_cast<const uint16_t *>(q), to_internal(kv), kv_lens,
@@ -136,7 +136,7 @@ int rollout_attn_decode_noalloc(const void *q, const ra_paged_kv *kv, const int3
   const int s = check_decode(q, kv, kv_lens, B, Hq, max_kv_len, scale, out);
   if (s != RA_OK) return s;
   if (B == 0) return RA_OK;
-  const ra::DecodePlan plan = ra::decode_plan(B, kv->num_kv_heads, max_kv_len);
+  const ra::DecodePlan plan = ra::decode_plan(B, kv->num_kv_heads, max_kv_len, true);
   if (ra::decode_workspace_bytes(B, Hq, plan) > RA_NOALLOC_SCRATCH_BYTES) return RA_ERR_WORKSPACE;
   void *ws = nullptr;
   const hipError_t e = device_scratch(&ws);
@@ -149,7 +149,7 @@ size_t rollout_attn_decode_shared_prefix_workspace_size(int32_t B, int32_t Hq, i
                                                         int32_t max_kv_len,
                                                         int32_t max_prefix_len) {
   if (B <= 0 || Hq <= 0 || Hkv <= 0 || max_kv_len < 0 || max_prefix_len < 0) return 0;
-  return ra::shared_prefix_workspace_bytes(B, Hq, ra::decode_plan(B, Hkv, max_kv_len),
+  return ra::shared_prefix_workspace_bytes(B, Hq, ra::decode_plan(B, Hkv, max_kv_len, true),
                                            max_prefix_len);
 }
 
@@ -172,7 +172,7 @@ int rollout_attn_decode_shared_prefix(const void *q, const ra_paged_kv *kv,
   if (B == 0) return RA_OK;
   if (num_groups == 0 || max_group_rows == 0 || max_group_rows > B || num_groups > B)
     return RA_ERR_SHAPE;
-  const ra::DecodePlan plan = ra::decode_plan(B, kv->num_kv_heads, max_kv_len);
+  const ra::DecodePlan plan = ra::decode_plan(B, kv->num_kv_heads, max_kv_len, true);
   const ra::SharedPrefixShape sh = ra::shared_prefix_shape(Hq / kv->num_kv_heads, num_groups,
                                                            max_group_rows, plan, max_prefix_len);
   // grid z holds the prefix planes and the row planes; prefix item indices

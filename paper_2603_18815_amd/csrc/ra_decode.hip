@@ -15,10 +15,14 @@ constexpr int kSplitWaves = 4;
 // KV head fastest: the Hkv workgroups of one (item, split) are dispatched
 // together, so the Hkv adjacent 4 KiB blocks of every page they read are
 // requested close in time (DRAM row locality).
-template <int NT, bool kPrefix, bool kFp8>
-__global__ __launch_bounds__(kSplitWaves * kWave, 2) void decode_split_kernel(DecodeArgs a) {
+// kDirect: every row is one split, whose result goes to out and lse.
+template <int NT, bool kFp8, bool kDirect>
+__global__ __launch_bounds__(kSplitWaves * kWave, 2) void decode_split_kernel(DecodeArgs a,
+                                                                             float *out,
+                                                                             float *lse) {
   __shared__ DecodeLds<NT, kSplitWaves> lds;
-  decode_split<NT, kPrefix, kSplitWaves, kFp8>(a, blockIdx.x, blockIdx.y, blockIdx.z, lds);
+  decode_split<NT, false, kSplitWaves, kFp8, kDirect>(a, blockIdx.x, blockIdx.y, blockIdx.z, lds,
+                                                      out, lse);
 }
 
 // Shared-prefix decode in one launch. Planes z < prefix_planes hold the
@@ -58,14 +62,15 @@ void launch_shared(bool fp8, dim3 grid, const DecodeArgs &a, const SharedPrefixS
                        stream, a, planes, sh.chunks, items);
 }
 
-template <int NT, bool kPrefix>
-void launch_split(bool fp8, dim3 grid, const DecodeArgs &a, hipStream_t stream) {
+template <int NT, bool kDirect>
+void launch_split(bool fp8, dim3 grid, const DecodeArgs &a, float *out, float *lse,
+                  hipStream_t stream) {
   if (fp8)
-    hipLaunchKernelGGL((decode_split_kernel<NT, kPrefix, true>), grid, dim3(kSplitWaves * kWave),
-                       0, stream, a);
+    hipLaunchKernelGGL((decode_split_kernel<NT, true, kDirect>), grid, dim3(kSplitWaves * kWave), 0,
+                       stream, a, out, lse);
   else
-    hipLaunchKernelGGL((decode_split_kernel<NT, kPrefix, false>), grid, dim3(kSplitWaves * kWave),
-                       0, stream, a);
+    hipLaunchKernelGGL((decode_split_kernel<NT, false, kDirect>), grid, dim3(kSplitWaves * kWave), 0,
+                       stream, a, out, lse);
 }
 
 // Split length forced by the environment (RA_SPLIT_TOKENS, for testing the
@@ -86,16 +91,32 @@ int64_t split_override() {
 
 }  // namespace
 
-DecodePlan decode_plan(int32_t B, int32_t hkv, int32_t max_kv_len) {
+// Calls with few (row, KV head) pairs (measured by graph replay, device time):
+// - rows of at most kDirectKeys keys are one split, whose workgroup writes the
+//   final result: no partials, no combine launch (4 rows of 32..256 keys 9.4 ->
+//   6.6 us, 64 rows of 100..500 keys 23.0 -> 19.1 us). At 300 keys two splits and
+//   a combine measure the same (7.4 against 7.5 us).
+// - longer rows are split down to 128 keys while there are fewer than kSmallItems
+//   items of the longest row's length: a split's four waves then take one page
+//   pair each instead of four in a chain (1 row of 1,000 keys, 8 KV heads: 12.4
+//   -> 7.6 us; 1 row of 4,096: 12.6 -> 9.0 us). Above that the shorter splits
+//   only add partials (2 rows of 16,000: 27.3 us with 512-key splits, 30.4 with
+//   256; 1 row of 65,000: 54 and 65 us).
+constexpr int kDirectKeys = 512;
+constexpr int kSmallItems = 256;
+
+DecodePlan decode_plan(int32_t B, int32_t hkv, int32_t max_kv_len, bool small) {
   // Aim for about 8k (row, KV head, split) items on the longest-row bound:
   // enough workgroups to balance rows of different lengths over 256 CUs,
   // long enough splits that the partial results stay well under 1 % of the
-  // KV bytes. Split lengths are powers of two in [512, 4096] keys, multiples
-  // of 128 keys (4 waves x one page pair), and depend only on the host-side
-  // sizes, never on page ids.
+  // KV bytes. Split lengths are powers of two in [512, 4096] keys (from 128 for
+  // the few items above), multiples of 128 keys (4 waves x one page pair), and
+  // depend only on the host-side sizes, never on page ids.
   int64_t work = (int64_t)B * hkv * (int64_t)(max_kv_len > 0 ? max_kv_len : 1);
   int64_t split = 512;
   while (split < 4096 && work / split > 8192) split *= 2;
+  if (small && max_kv_len > kDirectKeys)
+    while (split > 128 && work / split < kSmallItems) split /= 2;
   if (const int64_t forced = split_override()) split = forced;
   DecodePlan p;
   p.split_tokens = (int32_t)split;
@@ -126,12 +147,18 @@ hipError_t launch_decode(const uint16_t *q, const PagedKV &kv, const int32_t *kv
       make_decode_args(q, kv, kv_lens, B, hq, max_kv_len, scale, workspace, plan.max_splits, plan);
   // the G query heads of a KV head are the columns of one 16-column tile, or
   // of two for groups of 17 to 32 heads
-  if (a.group > 16)
-    launch_split<2, false>(kv.fp8, dim3(kv.hkv, plan.max_splits, B), a, stream);
+  const dim3 grid(kv.hkv, plan.max_splits, B);
+  const bool direct = plan.max_splits == 1;
+  if (a.group > 16 && direct)
+    launch_split<2, true>(kv.fp8, grid, a, out, lse, stream);
+  else if (a.group > 16)
+    launch_split<2, false>(kv.fp8, grid, a, out, lse, stream);
+  else if (direct)
+    launch_split<1, true>(kv.fp8, grid, a, out, lse, stream);
   else
-    launch_split<1, false>(kv.fp8, dim3(kv.hkv, plan.max_splits, B), a, stream);
+    launch_split<1, false>(kv.fp8, grid, a, out, lse, stream);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || direct) return e;
   hipLaunchKernelGGL(decode_combine_kernel, dim3(hq, B), dim3(kHeadDim), 0, stream, a, out, lse);
   return hipGetLastError();
 }

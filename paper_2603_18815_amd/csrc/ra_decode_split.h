@@ -26,8 +26,9 @@
 // Combine kernel: one workgroup per (row, query head) merges the slots in a
 // fixed order (prefix, then suffix):
 //   M = max_s m_s,  l = sum_s l_s 2^(m_s - M),  out = sum_s o_s 2^(m_s - M) / l.
-// It reads the slots eight at a time, so that a row's loads are in flight
-// together rather than one dependent round trip per slot.
+// The loads of up to 32 slots' partials go out together with those of all their
+// maxima and sums, the weights being worked out one slot per lane: a row costs
+// one or two round trips to memory however many slots it has.
 #pragma once
 
 #include "ra_device.h"
@@ -96,9 +97,11 @@ struct DecodeLds {
 // One split of KV head g (work item z: a row, or a group's row chunk), by a
 // workgroup of kW waves that all call it with the same arguments. kFp8: the
 // pools hold E4M3 codes, converted exactly to bf16 operands after the load.
-template <int NT, bool kPrefix, int kW, bool kFp8 = false>
+// kDirect: the row is one split, whose result is final (out, lse).
+template <int NT, bool kPrefix, int kW, bool kFp8 = false, bool kDirect = false>
 __device__ __forceinline__ void decode_split(const DecodeArgs &a, int g, int split, int z,
-                                             DecodeLds<NT, kW> &lds) {
+                                             DecodeLds<NT, kW> &lds, float *out = nullptr,
+                                             float *lse = nullptr) {
   // ---- what this workgroup computes: keys [t0, t1) of row krow's table for
   // the rows r0 .. r0 + nr - 1, into partial slot `slot`.
   int krow, r0, nr, t0, t1, slot;
@@ -126,6 +129,15 @@ __device__ __forceinline__ void decode_split(const DecodeArgs &a, int g, int spl
       t0 = gr.P + split * a.split_tokens;
       t1 = nr ? min(row_len(a, b), t0 + a.split_tokens) : t0;
       slot = a.prefix_slots + split;
+    }
+  }
+  if constexpr (kDirect) {
+    if (t0 >= t1) {   // an empty row
+      const size_t head = (size_t)r0 * a.hq + (size_t)g * a.group;
+      for (int idx = threadIdx.x; idx < a.group * kHeadDim; idx += kW * kWave)
+        out[head * kHeadDim + idx] = 0.f;
+      if (lse && (int)threadIdx.x < a.group) lse[head + threadIdx.x] = -INFINITY;
+      return;
     }
   }
   if (nr <= 0 || t0 >= t1) return;
@@ -341,7 +353,16 @@ __device__ __forceinline__ void decode_split(const DecodeArgs &a, int g, int spl
       lsum += f * s_l[w][c];
     }
     const int r = c / G;
-    const size_t part = ((size_t)(r0 + r) * a.hq + (size_t)g * G + (c - r * G)) * a.slots + slot;
+    const size_t head = (size_t)(r0 + r) * a.hq + (size_t)g * G + (c - r * G);
+    if constexpr (kDirect) {
+      // (the combine's weight of its only slot: 1, NaN for a max of -inf)
+      const float f = fast_exp2(M - M);
+      acc *= f, lsum *= f;
+      out[head * kHeadDim + d] = acc / lsum * a.v_scale;
+      if (lse && d == 0) lse[head] = (M + __log2f(lsum)) * kLn2;
+      continue;
+    }
+    const size_t part = head * a.slots + slot;
     a.ws_o[part * kHeadDim + d] = acc;
     if (d == 0) {
       a.ws_m[part] = M;
@@ -354,6 +375,7 @@ __device__ __forceinline__ void decode_split(const DecodeArgs &a, int g, int spl
 // this header.
 namespace {
 
+constexpr int kFewSlots = 8;
 __global__ __launch_bounds__(kHeadDim) void decode_combine_kernel(DecodeArgs a, float *out,
                                                                   float *lse) {
   const int h = blockIdx.x;
@@ -368,48 +390,81 @@ __global__ __launch_bounds__(kHeadDim) void decode_combine_kernel(DecodeArgs a, 
     P = gr.P;
     np = (P + a.split_tokens - 1) / a.split_tokens;
   }
-  const int d = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const size_t bh = (size_t)b * a.hq + h;
   const int ns = (row_len(a, b) - P + a.split_tokens - 1) / a.split_tokens;
   if (np + ns == 0) {
-    out[bh * kHeadDim + d] = 0.f;
-    if (lse && d == 0) lse[bh] = -INFINITY;
+    out[bh * kHeadDim + tid] = 0.f;
+    if (lse && tid == 0) lse[bh] = -INFINITY;
     return;
   }
-  const float *m = a.ws_m + bh * a.slots;
-  const float *l = a.ws_l + bh * a.slots;
-  const float *o = a.ws_o + bh * a.slots * kHeadDim + d;
   // slots in merge order: prefix splits [0, np), then suffix splits
   auto slot = [&](int s) { return s < np ? s : a.prefix_slots + (s - np); };
   const int n = np + ns;
+  const float *m = a.ws_m + bh * a.slots;
+  const float *l = a.ws_l + bh * a.slots;
+  if (n <= kFewSlots) {   // a thread per dim, all loads in flight together
+    float mv[kFewSlots], lv[kFewSlots], ov[kFewSlots], M = -INFINITY, acc = 0.f, lsum = 0.f;
+#pragma unroll
+    for (int s = 0; s < kFewSlots; ++s) {
+      const int k = slot(min(s, n - 1));
+      mv[s] = m[k];
+      lv[s] = l[k];
+      ov[s] = a.ws_o[(bh * a.slots + k) * kHeadDim + tid];
+    }
+#pragma unroll
+    for (int s = 0; s < kFewSlots; ++s) M = fmaxf(M, mv[s]);
+#pragma unroll
+    for (int s = 0; s < kFewSlots; ++s) {
+      const float f = fast_exp2(mv[s] - M);
+      acc += s < n ? f * ov[s] : 0.f;
+      lsum += s < n ? f * lv[s] : 0.f;
+    }
+    out[bh * kHeadDim + tid] = acc / lsum * a.v_scale;
+    if (lse && tid == 0) lse[bh] = (M + __log2f(lsum)) * kLn2;
+    return;
+  }
+  // quad q of the four 32-lane quads sums slots q, q + 4, ..., four dims a lane
+  const int quad = tid >> 5;
+  const float *o = a.ws_o + bh * a.slots * kHeadDim + 4 * (tid & 31);
   constexpr int kBatch = 8;
+  f32x4 ov[kBatch];
+  auto load = [&](int s0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j)
+      if (s0 + 4 * j + quad < n)
+        ov[j] = *reinterpret_cast<const f32x4 *>(o + (size_t)slot(s0 + 4 * j + quad) * kHeadDim);
+  };
+  load(0);   // in flight while the weights are worked out
+  // both waves work out the weights: lane i those of slots i, i + 64, ...
+  __shared__ float s_f[kWave], s_o[4][kHeadDim];
   float M = -INFINITY;
-  for (int s0 = 0; s0 < n; s0 += kBatch) {
-    float mv[kBatch];
+  for (int s = lane; s < n; s += kWave) M = fmaxf(M, m[slot(s)]);
 #pragma unroll
-    for (int j = 0; j < kBatch; ++j) mv[j] = s0 + j < n ? m[slot(s0 + j)] : -INFINITY;
+  for (int off = 1; off < kWave; off *= 2) M = fmaxf(M, __shfl_xor(M, off));
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  float lsum = 0.f;
+  for (int w0 = 0; w0 < n; w0 += kWave) {
+    const int s = w0 + lane;
+    const float f = s < n ? fast_exp2(m[slot(s)] - M) : 0.f;
+    if (s < n) lsum += f * l[slot(s)];
+    if (tid < kWave) s_f[lane] = f;
+    __syncthreads();
+    for (int s0 = w0; s0 < min(n, w0 + kWave); s0 += 4 * kBatch) {
+      if (s0 > 0) load(s0);
 #pragma unroll
-    for (int j = 0; j < kBatch; ++j) M = fmaxf(M, mv[j]);
-  }
-  float acc = 0.f, lsum = 0.f;
-  for (int s0 = 0; s0 < n; s0 += kBatch) {
-    float f[kBatch], ov[kBatch], lv[kBatch];
-#pragma unroll
-    for (int j = 0; j < kBatch; ++j) {
-      const bool ok = s0 + j < n;
-      const int k = slot(ok ? s0 + j : s0);
-      ov[j] = o[(size_t)k * kHeadDim];
-      lv[j] = l[k];
-      f[j] = ok ? fast_exp2(m[k] - M) : 0.f;
+      for (int j = 0; j < kBatch; ++j)
+        if (s0 + 4 * j + quad < n) acc += s_f[s0 - w0 + 4 * j + quad] * ov[j];
     }
-#pragma unroll
-    for (int j = 0; j < kBatch; ++j) {
-      acc += f[j] * ov[j];
-      lsum += f[j] * lv[j];
-    }
+    __syncthreads();   // s_f is written again
   }
-  out[bh * kHeadDim + d] = acc / lsum * a.v_scale;
-  if (lse && d == 0) lse[bh] = (M + __log2f(lsum)) * kLn2;
+#pragma unroll
+  for (int off = 1; off < kWave; off *= 2) lsum += __shfl_xor(lsum, off);
+  *reinterpret_cast<f32x4 *>(&s_o[quad][4 * (tid & 31)]) = acc;
+  __syncthreads();
+  const float sum = ((s_o[0][tid] + s_o[1][tid]) + s_o[2][tid]) + s_o[3][tid];
+  out[bh * kHeadDim + tid] = sum / lsum * a.v_scale;
+  if (lse && tid == 0) lse[bh] = (M + __log2f(lsum)) * kLn2;
 }
 
 }  // namespace

@@ -1,0 +1,73 @@
+"""GPU parity of decode at the sizes where its split and its merge change.
+
+Rows of up to 512 keys are one split whose result is final; longer ones are split
+into at least 128 keys, more finely the fewer rows and KV heads there are, and
+merged one slot per step (up to 8 slots) or one slot per lane (32, 64 and more).
+Each call mixes lengths (empty rows and single keys among them) and is compared
+with the fp64 oracle at the decode tolerance; the same rows as one-row groups
+without a shared prefix must give the same bits.
+"""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2603_18815_amd as ra
+import synth
+from tests.gpu_util import DECODE_LSE_ATOL, assert_attn_close, bits
+
+pytestmark = pytest.mark.gpu
+SCALE = 1.0 / math.sqrt(128)
+
+CASES = [
+    (8, 2, [256, 0, 1, 511, 512, 33]),       # final splits, an empty row
+    (17, 1, [512, 0, 100]),                  # the same in two 16-column tiles
+    (4, 4, [513, 0, 128, 129, 512]),         # 5 slots of 128 keys
+    (8, 1, [1024, 1000, 31]),                # 8 slots: the last small merge
+    (8, 1, [1025, 4000, 4097]),              # 9, 32 and 33 slots
+    (32, 1, [8192, 8193, 0, 5]),             # 64 and 65 slots, two tiles
+    (1, 1, [20000, 17]),                     # 157 slots
+    (32, 8, [16000, 16001]),                 # more heads: longer splits
+]
+
+
+def i32(x, dev):
+    return torch.as_tensor(np.ascontiguousarray(np.asarray(x, np.int32)), device=dev)
+
+
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("Hq,Hkv,lens", CASES)
+def test_decode_splits_vs_oracle(device, Hq, Hkv, lens, fp8):
+    print(f"[gpu-test] decode splits Hq={Hq} Hkv={Hkv} lens={lens} fp8={fp8}", flush=True)
+    w = synth.decode_workload(23, len(lens), Hq, Hkv, lambda r, n: np.asarray(lens), "splits")
+    t = synth.make_tensors(w, device)
+    k, v, scales = t.k_pool, t.v_pool, ()
+    if fp8:
+        gen = synth.value_generator(24, device)
+        scales = (0.02, 0.015)
+        k = synth.randn_fp8_codes(k.shape, gen, device, scales[0])
+        v = synth.randn_fp8_codes(v.shape, gen, device, scales[1])
+    synth.poison_unowned(k, v, w.layout)
+    kv = ra.PagedKV(k, v, i32(w.decode_table(), device), *scales)
+    kl, mk, B = i32(lens, device), max(lens), len(lens)
+    out, lse = ra.decode(t.q_decode, kv, kl, mk, SCALE, want_lse=True)
+    out2 = torch.empty_like(out)
+    ra.decode_noalloc(t.q_decode, kv, kl, mk, out2, SCALE)
+    groups = i32(np.arange(B + 1), device)
+    out3, lse3 = ra.decode_shared_prefix(t.q_decode, kv, kl, groups, i32([0] * B, device), 1, 0, mk,
+                                         SCALE, want_lse=True)
+    torch.cuda.synchronize()
+    assert torch.equal(out, out2), "no-allocation decode differs"
+    assert torch.equal(out, out3) and torch.equal(lse, lse3), "one-row groups differ"
+    if fp8:
+        ref, ref_lse = oracle.decode_fp8(bits(t.q_decode), bits(k), bits(v), *scales,
+                                         w.decode_table(), np.asarray(lens), SCALE)
+    else:
+        ref, ref_lse = oracle.decode(bits(t.q_decode), bits(k), bits(v), w.decode_table(),
+                                     np.asarray(lens), SCALE)
+    rows = np.asarray(lens) > 0
+    assert torch.all(out[~rows] == 0) and torch.all(torch.isneginf(lse[~rows]))
+    assert_attn_close(out.cpu().numpy()[rows], ref[rows], "decode splits")
+    np.testing.assert_allclose(lse.cpu().numpy()[rows], ref_lse[rows], atol=DECODE_LSE_ATOL, rtol=0)
