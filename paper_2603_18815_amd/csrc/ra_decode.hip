@@ -99,11 +99,15 @@ int64_t split_override() {
 // - longer rows are split down to 128 keys while there are fewer than kSmallItems
 //   items of the longest row's length: a split's four waves then take one page
 //   pair each instead of four in a chain (1 row of 1,000 keys, 8 KV heads: 12.4
-//   -> 7.6 us; 1 row of 4,096: 12.6 -> 9.0 us). Above that the shorter splits
+//   -> 7.6 us; 1 row of 4,096: 12.6 -> 8.8 us). Above that the shorter splits
 //   only add partials (2 rows of 16,000: 27.3 us with 512-key splits, 30.4 with
-//   256; 1 row of 65,000: 54 and 65 us).
+//   256; 1 row of 65,000: 54 and 65 us). The longest row keeps at most
+//   kSmallSlots slots: its combine reads them in rounds (1 row of 30,000 keys, 1
+//   KV head: 17.4 us with 59 slots, 29.4 with 235; 1 row of 8,000, 2 KV heads:
+//   10.2 with 32 slots, 11.1 with 63, 13.2 with 16).
 constexpr int kDirectKeys = 512;
 constexpr int kSmallItems = 256;
+constexpr int kSmallSlots = 32;
 
 DecodePlan decode_plan(int32_t B, int32_t hkv, int32_t max_kv_len, bool small) {
   // Aim for about 8k (row, KV head, split) items on the longest-row bound:
@@ -116,7 +120,8 @@ DecodePlan decode_plan(int32_t B, int32_t hkv, int32_t max_kv_len, bool small) {
   int64_t split = 512;
   while (split < 4096 && work / split > 8192) split *= 2;
   if (small && max_kv_len > kDirectKeys)
-    while (split > 128 && work / split < kSmallItems) split /= 2;
+    while (split > 128 && work / split < kSmallItems && 2 * (int64_t)max_kv_len <= kSmallSlots * split)
+      split /= 2;
   if (const int64_t forced = split_override()) split = forced;
   DecodePlan p;
   p.split_tokens = (int32_t)split;
@@ -159,7 +164,7 @@ hipError_t launch_decode(const uint16_t *q, const PagedKV &kv, const int32_t *kv
     launch_split<1, false>(kv.fp8, grid, a, out, lse, stream);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || direct) return e;
-  hipLaunchKernelGGL(decode_combine_kernel, dim3(hq, B), dim3(kHeadDim), 0, stream, a, out, lse);
+  launch_combine(a, B, out, lse, stream);
   return hipGetLastError();
 }
 
@@ -202,8 +207,7 @@ hipError_t launch_decode_shared_prefix(const uint16_t *q, const PagedKV &kv,
     launch_shared<1>(kv.fp8, grid, a, sh, stream);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(decode_combine_kernel, dim3(hq, (unsigned)sh.row_z), dim3(kHeadDim), 0, stream,
-                     a, out, lse);
+  launch_combine(a, (unsigned)sh.row_z, out, lse, stream);
   return hipGetLastError();
 }
 

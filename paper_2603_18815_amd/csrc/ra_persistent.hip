@@ -659,14 +659,14 @@ hipError_t launch_mixed(const uint16_t *q_decode, const PagedKV &kv_decode,
     }
   }
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (B_append > 0) {
+  // (line mode needs a tile of more than kLineCost key blocks)
+  if (B_append > 0 && tile_blocks > kLineCost) {
     hipLaunchKernelGGL(append_merge_kernel, dim3(kShares, kMergeParts), dim3(kMergeThreads), 0,
                        stream, m);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   if (B_decode == 0) return hipSuccess;
-  hipLaunchKernelGGL(dsplit::decode_combine_kernel, dim3(hq, B_decode), dim3(kHeadDim), 0, stream,
-                     m.de, out_decode, lse_decode);
+  dsplit::launch_combine(m.de, B_decode, out_decode, lse_decode, stream);
   return hipGetLastError();
 }
 
