@@ -22,7 +22,13 @@
 //   alternative being 128 x 128 tiles that load W again for every 128 tokens).
 //   Blocks of 192 tokens where that holds the batch (257 tokens, row-major: 544
 //   us in blocks of 256, 470 us in blocks of 192).
-// - N >= 512: logprob_tile_kernel, 384 x 256 tiles with h staged.
+// - N >= 512: logprob_tile_kernel, 384 x 256 tiles with h staged. When the last
+//   round of tiles would leave over half of the 256 compute units idle, its
+//   tiles are cut along the tokens, 128 or 64 each, so that the round is short
+//   too (its partial results stay where they are, one per token and chunk): 1,000
+//   tokens 1,094 -> 1,073 us (48 tiles of 256 tokens became 192 of 64), 512
+//   tokens 618 -> 597, 2,048 tokens 2,066 -> 2,042 us. Cutting them along D or
+//   the vocabulary costs partial logits or partials.
 //
 // logprob_partial_kernel: each wave computes the logits of its 32 vocabulary
 // rows for the batch's tokens on the matrix cores (4 or 2 tiles of
@@ -79,7 +85,7 @@ struct LogprobArgs {
   float *ws_l;    // [N][chunks] sum of 2^(y - max)
   float *tgt;     // [N] logit of the target (natural units)
   int32_t N, V, D, chunks, token_blocks;
-  int32_t tall;       // logprob_rounds_kernel: chunks of 384 rows before the shorter ones
+  int32_t tall;       // chunks of 384 rows in whole 256-token (or largest) tiles before the last round
   float scale;        // logits = scale * <h, W_v>
   float scale_log2;   // scale * log2(e)
 };
@@ -298,7 +304,6 @@ constexpr int kTileDims = 32;         // dims per step
 constexpr int kTileStages = 3;
 constexpr int kTileElems = kTileRows * kTileDims;     // token region of a stage (16 KB)
 constexpr int kTileElemsA = kTileRowsA * kTileDims;   // vocabulary region (24 KB)
-constexpr int kLoadsB = kTileRows / 16 / kTileWaves;   // 2
 // Refill load d of a step goes after this one of the step's products.
 template <int kLoads, int kProducts>
 __device__ constexpr int load_after(int d) {
@@ -337,8 +342,8 @@ __device__ __forceinline__ void load_lds16_stream(const uint16_t *g, uint32_t ld
 }
 
 // One tile: RT 32-row tiles per wave (128 RT vocabulary rows from v0) x TT
-// 32-token tiles per wave (64 TT tokens, block tblock), partial results into
-// column `part`. kStagedH: h from
+// 32-token tiles per wave (64 TT tokens: part `sub` of token block tblock),
+// partial results into column `part`. kStagedH: h from
 // its staged copy (the workspace holds one from N = kTileMinN on), otherwise
 // from its rows, 64 bytes at a time like a row-major W.
 struct TileLds {
@@ -348,16 +353,17 @@ struct TileLds {
   float l[4][kTileRows];
 };
 template <bool kPacked, bool kStagedH, int RT, int TT>
-__device__ __forceinline__ void logprob_tile(const LogprobArgs &a, int v0, int tblock, int part,
-                                             TileLds &lds) {
+__device__ __forceinline__ void logprob_tile(const LogprobArgs &a, int v0, int tblock, int sub,
+                                             int part, TileLds &lds) {
   auto &sA = lds.a;
   auto &sB = lds.b;
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   constexpr int kTokens = 64 * TT;
-  static_assert(TT == 4 || !kStagedH, "the staged copy holds blocks of 256 tokens");
-  const int t0 = tblock * kTokens;
-  constexpr int kLoadsA = RT;
+  const int t0 = kStagedH ? tblock * kTileRows + sub * kTokens : tblock * kTokens;
+  // load instructions (16 rows each) of a wave and step; of a 64-token tile's
+  // four h instructions each is issued by two waves
+  constexpr int kLoadsA = RT, kLoadsB = (TT + 1) / 2;
 
   // ---- loads: instructions kLoadsA * wave + k of the W region, kLoadsB *
   // wave + k of the h region ----
@@ -375,17 +381,21 @@ __device__ __forceinline__ void logprob_tile(const LogprobArgs &a, int v0, int t
                     : a.W + (size_t)v * a.D + 8 * lc;
   }
   const int nsteps = a.D / kTileDims;
+  auto h_instr = [&](int k) __attribute__((always_inline)) {
+    return TT == 1 ? wave % 4 : kLoadsB * wave + k;
+  };
   // a staged copy of h holds each (token block, step) as the 16 KB image of
   // its LDS region: load instruction j reads 1 KB contiguous
 #pragma unroll
   for (int k = 0; k < kLoadsB; ++k) {
-    const int j = kLoadsB * wave + k, r = 16 * j + lane / 4;
+    const int j = h_instr(k), r = 16 * j + lane / 4;
     const int lc = (lane % 4) ^ ((r >> 2) & 3);
-    gb[k] = kStagedH ? a.hp + (size_t)tblock * nsteps * kTileElems + (size_t)j * 512 + lane * 8
+    gb[k] = kStagedH ? a.hp + (size_t)tblock * nsteps * kTileElems + (size_t)(4 * TT * sub + j) * 512 +
+                           lane * 8
                      : a.h + (size_t)min(t0 + min(r, kTokens - 1), a.N - 1) * a.D + 8 * lc;
   }
   const int last = nsteps - 1;
-  const uint32_t blkA = (uint32_t)(kLoadsA * wave) * 1024u, blkB = (uint32_t)(kLoadsB * wave) * 1024u;
+  const uint32_t blkA = (uint32_t)(kLoadsA * wave) * 1024u;
   // offsets (elements) of step s in W and h; steps past the last repeat it
   // (branch-free, so that every step issues the same number of loads)
   // elements per 64-dim step of the packed copy (all of its 32-row tiles)
@@ -399,7 +409,7 @@ __device__ __forceinline__ void logprob_tile(const LogprobArgs &a, int v0, int t
       load_lds16(ga[d] + w_off(s), lds_address(sA[st]) + blkA + 1024u * d);
     else
       load_lds16(gb[d - kLoadsA] + (size_t)s * (kStagedH ? kTileElems : kTileDims),
-                 lds_address(sB[st]) + blkB + 1024u * (d - kLoadsA));
+                 lds_address(sB[st]) + 1024u * h_instr(d - kLoadsA));
   };
   constexpr int kLoadsPerStep = kLoadsA + kLoadsB;
   constexpr int kProducts = 2 * RT * TT;
@@ -513,15 +523,21 @@ __device__ __forceinline__ void logprob_tile(const LogprobArgs &a, int v0, int t
   }
 }
 
-template <bool kPacked>
+// `tall` chunks in 256-token tiles, then the rest in tiles of 64 TT tokens.
+template <bool kPacked, int TT>
 __global__ __launch_bounds__(kTileThreads, 1) void logprob_tile_kernel(LogprobArgs a) {
-  const int id = blockIdx.x;
-  const int xcd = id % kXcds, slot = id / kXcds;
-  const int chunk = (slot / a.token_blocks) * kXcds + xcd;
-  const int tblock = slot - (slot / a.token_blocks) * a.token_blocks;
-  if (chunk >= a.chunks) return;
   __shared__ TileLds lds;
-  logprob_tile<kPacked, true, 3, 4>(a, chunk * kTileRowsA, tblock, chunk, lds);
+  const int whole = TT == 4 ? 0x7fffffff : a.tall * a.token_blocks;
+  const bool split = (int)blockIdx.x >= whole;
+  const int id = blockIdx.x - (split ? whole : 0), parts = split ? 4 / TT : 1;
+  const int xcd = id % kXcds, slot = id / kXcds, per = a.token_blocks * parts;
+  const int chunk = (split ? a.tall : 0) + (slot / per) * kXcds + xcd;
+  const int s = slot - (slot / per) * per;
+  if (chunk >= a.chunks) return;
+  if (!split)
+    logprob_tile<kPacked, true, 3, 4>(a, chunk * kTileRowsA, s, 0, chunk, lds);
+  else
+    logprob_tile<kPacked, true, 3, TT>(a, chunk * kTileRowsA, s / parts, s % parts, chunk, lds);
 }
 
 // Tiles of two heights: `tall` chunks of 384 rows, then chunks of 128 RT rows.
@@ -534,10 +550,10 @@ __global__ __launch_bounds__(kTileThreads, 1) void logprob_rounds_kernel(Logprob
   if (chunk >= a.chunks) return;
   __shared__ TileLds lds;
   if (RT == 3 || chunk < a.tall)
-    logprob_tile<kPacked, false, 3, TT>(a, chunk * kTileRowsA, tblock, chunk, lds);
+    logprob_tile<kPacked, false, 3, TT>(a, chunk * kTileRowsA, tblock, 0, chunk, lds);
   else
     logprob_tile<kPacked, false, RT, TT>(
-        a, a.tall * kTileRowsA + (chunk - a.tall) * 128 * RT, tblock, chunk, lds);
+        a, a.tall * kTileRowsA + (chunk - a.tall) * 128 * RT, tblock, 0, chunk, lds);
 }
 
 // ---- small batches over a row-major W: one pass of W through LDS ----
@@ -737,6 +753,20 @@ Rounds logprob_rounds(int32_t token_blocks, int32_t V) {
   r.rest = (int32_t)((left + r.rt - 1) / r.rt);
   return r;
 }
+// N >= kTileMinN: `whole` chunks (a multiple of 8) in 256-token tiles, the rest in
+// tiles of 64 groups tokens when those still fit the compute units at once.
+struct LastRound {
+  int32_t whole;
+  int groups;
+};
+LastRound logprob_last_round(int32_t token_blocks, int32_t chunks) {
+  const int64_t tiles = (int64_t)chunks * token_blocks;
+  LastRound r;
+  r.whole = (int32_t)(tiles / kTileCus * kTileCus / token_blocks / kXcds * kXcds);
+  const int64_t rest = (int64_t)(chunks - r.whole) * token_blocks;
+  r.groups = rest == 0 || rest > kTileCus / 2 ? 4 : rest > kTileCus / 4 ? 2 : 1;
+  return r;
+}
 bool logprob_in_rounds(int32_t N) { return N > kRoundsMinN && N < kTileMinN; }
 int32_t token_blocks_of(int32_t N) { return (N + kTileRows - 1) / kTileRows; }
 // 64-token groups of a token block (3 or 4)
@@ -858,10 +888,27 @@ hipError_t launch_logprob(const uint16_t *h, const uint16_t *W, const int32_t *t
       RA_ROUNDS(11, true, 3, 4)
 #undef RA_ROUNDS
     }
-  } else if (N >= kTileMinN && packed)
-    hipLaunchKernelGGL(logprob_tile_kernel<true>, grid, dim3(kTileThreads), 0, stream, a);
-  else if (N >= kTileMinN)
-    hipLaunchKernelGGL(logprob_tile_kernel<false>, grid, dim3(kTileThreads), 0, stream, a);
+  } else if (N >= kTileMinN) {
+    const LastRound r = logprob_last_round(a.token_blocks, a.chunks);
+    a.tall = r.whole;
+    const int64_t rest = (a.chunks - r.whole + kXcds - 1) / kXcds * kXcds;
+    const dim3 tiles = r.groups == 4 ? grid
+                                     : dim3((unsigned)(((int64_t)r.whole + rest * (4 / r.groups)) *
+                                                       a.token_blocks));
+    switch ((packed ? 3 : 0) + (r.groups == 4 ? 2 : r.groups - 1)) {
+#define RA_TILES(X, P, TT)                                                                       \
+  case X:                                                                                        \
+    hipLaunchKernelGGL((logprob_tile_kernel<P, TT>), tiles, dim3(kTileThreads), 0, stream, a); \
+    break;
+      RA_TILES(0, false, 1)
+      RA_TILES(1, false, 2)
+      RA_TILES(2, false, 4)
+      RA_TILES(3, true, 1)
+      RA_TILES(4, true, 2)
+      RA_TILES(5, true, 4)
+#undef RA_TILES
+    }
+  }
   else if (packed && tiles == 2)
     hipLaunchKernelGGL((logprob_partial_kernel<2>), grid, dim3(kLpThreads), 0, stream, a);
   else if (packed)

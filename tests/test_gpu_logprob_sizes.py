@@ -3,7 +3,8 @@
 Up to 128 tokens a row-major head goes through LDS (4 or 8 waves, 64 or 128
 tokens); from 129 to 511 tokens tiles of 384 vocabulary rows fill the 256 compute
 units and lower ones (128, 256 or 384 rows) take the rest, in one or two blocks of
-up to 192 or 256 tokens. Every case is compared with the fp64 oracle (tolerance as
+up to 192 or 256 tokens; from 512 tokens the last round's tiles may be cut along
+the tokens. Every case is compared with the fp64 oracle (tolerance as
 in tests.test_gpu_logprob) and, bit for bit, with the packed head.
 """
 import numpy as np
@@ -27,6 +28,9 @@ SIZES = [
     # two token blocks (128 chunks a round)
     (257, 49152 + 1, 128), (384, 49152 + 128 * 200, 64), (385, 49152 + 128 * 300 + 77, 64),
     (511, 3000, 320),
+    # N >= 512: the last round of tiles in 64- or 128-token parts, alone and after a full one
+    (512, 1000, 64), (520, 11000, 64), (1000, 384 * 70, 64), (1000, 384 * 86 - 50, 64),
+    (700, 384 * 50, 64),                    # over half a round: whole tiles
 ]
 
 
