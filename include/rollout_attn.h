@@ -141,7 +141,11 @@ const char *ra_status_string(int status);
  *   lse         fp32 [B][Hq] or NULL
  *   workspace   device scratch of at least
  *               rollout_attn_decode_workspace_size(B, Hq, Hkv, max_kv_len) bytes
- *               (split partial results; contents on entry are ignored)
+ *               (split partial results; contents on entry are ignored). The
+ *               size is that of the fastest splits and can fall as B or
+ *               max_kv_len grows; a workspace sized for a larger call of the
+ *               same Hq and Hkv is always enough where 512-key splits fit it:
+ *               the splits are lengthened until their partials fit.
  * Errors: RA_ERR_NULL, RA_ERR_SHAPE (B < 0, Hq % Hkv, max_kv_len > bt_stride*16),
  *         RA_ERR_UNSUPPORTED, RA_ERR_WORKSPACE, RA_ERR_HIP.
  */

@@ -98,6 +98,18 @@ int check_decode(const void *q, const ra_paged_kv *kv, const int32_t *kv_lens, i
   return RA_OK;
 }
 
+// Doubles the split length of a plan with shorter splits; false once it is the plain
+// plan's. A workspace sized for other shapes (more rows, longer rows) may hold fewer
+// slots than the shorter splits need, but then holds the plain plan's: 9 rows of up to
+// 4,096 keys over one KV head want 16 slots a row, 16 such rows 8.
+bool coarsen_plan(ra::DecodePlan *plan, int32_t B, int32_t hkv, int32_t max_kv_len) {
+  if (plan->split_tokens >= ra::decode_plan(B, hkv, max_kv_len).split_tokens) return false;
+  plan->split_tokens *= 2;
+  plan->max_splits =
+      (int32_t)(((int64_t)max_kv_len + plan->split_tokens - 1) / plan->split_tokens);
+  return true;
+}
+
 }  // namespace
 
 extern "C" {
@@ -122,9 +134,10 @@ int rollout_attn_decode(const void *q, const ra_paged_kv *kv, const int32_t *kv_
   const int s = check_decode(q, kv, kv_lens, B, Hq, max_kv_len, scale, out);
   if (s != RA_OK) return s;
   if (B == 0) return RA_OK;
-  const ra::DecodePlan plan = ra::decode_plan(B, kv->num_kv_heads, max_kv_len, true);
-  if (!workspace || workspace_bytes < ra::decode_workspace_bytes(B, Hq, plan))
-    return RA_ERR_WORKSPACE;
+  ra::DecodePlan plan = ra::decode_plan(B, kv->num_kv_heads, max_kv_len, true);
+  if (!workspace) return RA_ERR_WORKSPACE;
+  while (workspace_bytes < ra::decode_workspace_bytes(B, Hq, plan))
+    if (!coarsen_plan(&plan, B, kv->num_kv_heads, max_kv_len)) return RA_ERR_WORKSPACE;
   return hip_status(ra::launch_decode(static_cast<const uint16_t *>(q), to_internal(kv), kv_lens,
                                       B, Hq, max_kv_len, scale, out, lse, workspace, plan,
                                       stream));
@@ -172,17 +185,20 @@ int rollout_attn_decode_shared_prefix(const void *q, const ra_paged_kv *kv,
   if (B == 0) return RA_OK;
   if (num_groups == 0 || max_group_rows == 0 || max_group_rows > B || num_groups > B)
     return RA_ERR_SHAPE;
-  const ra::DecodePlan plan = ra::decode_plan(B, kv->num_kv_heads, max_kv_len, true);
-  const ra::SharedPrefixShape sh = ra::shared_prefix_shape(Hq / kv->num_kv_heads, num_groups,
-                                                           max_group_rows, plan, max_prefix_len);
-  // grid z holds the prefix planes and the row planes; prefix item indices
-  // (plane x max_splits + split) must fit an int
-  if (sh.prefix_planes + sh.row_z > kMaxGridYZ ||
-      sh.prefix_planes * plan.max_splits > INT32_MAX)
-    return RA_ERR_UNSUPPORTED;
-  if (!workspace ||
-      workspace_bytes < ra::shared_prefix_workspace_bytes(B, Hq, plan, max_prefix_len))
-    return RA_ERR_WORKSPACE;
+  ra::DecodePlan plan = ra::decode_plan(B, kv->num_kv_heads, max_kv_len, true);
+  for (;;) {
+    const ra::SharedPrefixShape sh = ra::shared_prefix_shape(Hq / kv->num_kv_heads, num_groups,
+                                                             max_group_rows, plan, max_prefix_len);
+    // grid z holds the prefix planes and the row planes; prefix item indices
+    // (plane x max_splits + split) must fit an int
+    const bool fits = sh.prefix_planes + sh.row_z <= kMaxGridYZ &&
+                      sh.prefix_planes * plan.max_splits <= INT32_MAX;
+    if (fits && workspace &&
+        workspace_bytes >= ra::shared_prefix_workspace_bytes(B, Hq, plan, max_prefix_len))
+      break;
+    if (!coarsen_plan(&plan, B, kv->num_kv_heads, max_kv_len))
+      return fits ? RA_ERR_WORKSPACE : RA_ERR_UNSUPPORTED;
+  }
   return hip_status(ra::launch_decode_shared_prefix(
       static_cast<const uint16_t *>(q), to_internal(kv), kv_lens, group_start, prefix_len, B, Hq,
       num_groups, max_group_rows, max_prefix_len, max_kv_len, scale, out, lse, workspace, plan,

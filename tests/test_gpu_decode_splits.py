@@ -71,3 +71,37 @@ def test_decode_splits_vs_oracle(device, Hq, Hkv, lens, fp8):
     assert torch.all(out[~rows] == 0) and torch.all(torch.isneginf(lse[~rows]))
     assert_attn_close(out.cpu().numpy()[rows], ref[rows], "decode splits")
     np.testing.assert_allclose(lse.cpu().numpy()[rows], ref_lse[rows], atol=DECODE_LSE_ATOL, rtol=0)
+
+
+@pytest.mark.parametrize("B,Hkv,mk,rows", [(9, 1, 4096, 16), (3, 8, 4096, 4), (5, 8, 1000, 9), (1, 2, 4096, 1)])
+def test_workspace_of_other_shapes(device, B, Hkv, mk, rows):
+    """A workspace that holds splits of 512 keys for the call's rows, such as one sized for
+    more rows, is enough: the shorter splits are taken only as far as it holds them."""
+    print(f"[gpu-test] workspace of other shapes B={B} Hkv={Hkv} mk={mk}", flush=True)
+    Hq = 4 * Hkv
+    lens = np.linspace(mk, 1, B).astype(np.int64)
+    w = synth.decode_workload(25, B, Hq, Hkv, lambda r, n: lens, "ws")
+    t = synth.make_tensors(w, device)
+    kv = ra.PagedKV(t.k_pool, t.v_pool, i32(w.decode_table(), device))
+    kl = i32(lens, device)
+    slots = (mk + 511) // 512
+    least = B * Hq * slots * 130 * 4
+    full = ra.decode_workspace_size(B, Hq, Hkv, mk)
+    assert full > least
+    ref, ref_lse = oracle.decode(bits(t.q_decode), bits(t.k_pool), bits(t.v_pool),
+                                 w.decode_table(), lens, SCALE)
+    for size in {least, min(full, max(least, ra.decode_workspace_size(rows, Hq, Hkv, mk)))}:
+        ws = torch.full((size + 4096,), 255, dtype=torch.uint8, device=device)
+        out, lse = ra.decode(t.q_decode, kv, kl, mk, SCALE, want_lse=True, workspace=ws[:size])
+        torch.cuda.synchronize()
+        assert torch.all(ws[size:] == 255), "written past the workspace"
+        assert_attn_close(out.cpu().numpy(), ref, "smaller workspace")
+        np.testing.assert_allclose(lse.cpu().numpy(), ref_lse, atol=DECODE_LSE_ATOL, rtol=0)
+        two = i32([0, (B + 1) // 2, B] if B > 1 else [0, 1], device)
+        ng = two.numel() - 1
+        same = ra.decode_shared_prefix(t.q_decode, kv, kl, two, i32([0] * ng, device),
+                                       (B + 1) // 2, 0, mk, SCALE, workspace=ws[:size])[0]
+        assert torch.equal(same, out), "groups without a prefix differ"
+    ws = torch.empty(least - 1, dtype=torch.uint8, device=device)
+    with pytest.raises(ra.RolloutAttnError, match="RA_ERR_WORKSPACE"):
+        ra.decode(t.q_decode, kv, kl, mk, SCALE, workspace=ws)
