@@ -25,6 +25,12 @@
 // reduction and no cross-lane exchange. The causal mask (key position >
 // ctx + i) is applied only on blocks that reach past the wave's first query
 // position.
+// A piece of a tile that starts at a later key block takes its weights against
+// the max of the tile's first pair of pages, where an uncut tile's running max
+// starts: the weights are then rounded to bf16 as in the uncut tile (unless the
+// max moves on the way), and cutting a tile changes its result by the order of
+// fp32 sums alone (2e-7 to 5e-7 of the result's norm, 2e-3 before; 2 rows of 64..512
+// new tokens over 2k..24k keys; 209 -> 211 us).
 #pragma once
 
 #include <type_traits>
@@ -347,7 +353,32 @@ __device__ __forceinline__ void append_tile(const AppendArgs &a, const AppendTil
   *reinterpret_cast<u32x4 *>(
       &sV[buffer(kb0 + kBuffers - 1) * kBlockElems + kBlockElems / 2 + 8 * tid]) = u32x4{};
   stage_load(kb0);
+  // A piece that does not start its tile also takes K of the tile's first pair of pages:
+  // into the K buffer before the first block's, which block kb0 + 3 overwrites after a
+  // barrier that follows the use.
+  const int first_buf = buffer(kb0 + kBuffers - 1);
+  u32x4 first_k = {};
+  const int first_page = kFp8 ? f_page : st_page;
+  const bool first_pair = kb0 > 0 && first_page < 2;
+  if (__builtin_expect(first_pair, 0)) {
+    const size_t base = ((size_t)clamp_page(bt[first_page], a.num_pages) * a.hkv + g) * head_stride;
+    if constexpr (kFp8)
+      first_k = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const uint8_t *>(a.k_pool) +
+                                                 base + f_koff);
+    else
+      first_k = load_u32x4(a.k_pool + base + k_off);
+  }
   stage_store(kb0, buffer(kb0));
+  if (__builtin_expect(first_pair, 0)) {
+    uint16_t *kl = sK + first_buf * kKBlockElems;
+    if constexpr (kFp8) {
+      kl += k_lds(f_page * kPage + f_slot, 2 * f_c16);
+      *reinterpret_cast<bf16x8 *>(kl) = fp8x8_to_bf16x8(u32x2{first_k[0], first_k[1]});
+      *reinterpret_cast<bf16x8 *>(kl + 8) = fp8x8_to_bf16x8(u32x2{first_k[2], first_k[3]});
+    } else {
+      *reinterpret_cast<u32x4 *>(kl + k_lds(st_page * kPage + st_slot, st_kch)) = first_k;
+    }
+  }
   if (kb0 + 1 < nblocks) {
     stage_load(kb0 + 1);
     stage_store(kb0 + 1, buffer(kb0 + 1));
@@ -362,6 +393,23 @@ __device__ __forceinline__ void append_tile(const AppendArgs &a, const AppendTil
       __syncthreads();
     }
     return;
+  }
+  // Max (base 2) of the scores sc over the 32 keys of a pair, per query row.
+  auto pair_scores_max = [&](const float *sc) __attribute__((always_inline)) {
+    float mx = fmaxf(fmaxf(sc[0], sc[1]), sc[2]);
+#pragma unroll
+    for (int r = 3; r < 15; r += 2) mx = fmaxf(fmaxf(mx, sc[r]), sc[r + 1]);
+    mx = pair_max(fmaxf(mx, sc[15]));
+    return kPosScale ? mx * c2 : mx;
+  };
+  if (__builtin_expect(kb0 > 0, 0)) {
+    // (no mask: a query that sees a key of block kb0 sees all of block 0)
+    const f32x16 s0 = scores(first_buf, 0);
+    float sc[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sc[r] = kPosScale ? s0[r] : s0[r] * c2;
+    m_run = pair_scores_max(sc);
+    if (m_run == -INFINITY) m_run = 0.f;
   }
   f32x16 st = scores(buffer(kb0), 0);
   bf16x8 pb0 = bf16x8{}, pb1 = bf16x8{};   // weights of the previous pair (none yet)
@@ -425,13 +473,7 @@ __device__ __forceinline__ void append_tile(const AppendArgs &a, const AppendTil
     };
     weights();
     if (!__all(psum <= kSumLimit)) {
-      float mx = fmaxf(fmaxf(sc[0], sc[1]), sc[2]);
-#pragma unroll
-      for (int r = 3; r < 15; r += 2) mx = fmaxf(fmaxf(mx, sc[r]), sc[r + 1]);
-      mx = fmaxf(mx, sc[15]);
-      mx = pair_max(mx);
-      if (kPosScale) mx *= c2;
-      float m_new = fmaxf(m_run, mx);
+      float m_new = fmaxf(m_run, pair_scores_max(sc));
       if (m_new == -INFINITY) m_new = 0.f;   // nothing attended yet: any finite reference
       const float alpha = fast_exp2(m_run - m_new);
       m_run = m_new;

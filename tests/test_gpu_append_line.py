@@ -19,6 +19,7 @@ import oracle
 import paper_2603_18815_amd as ra
 import synth
 from tests.gpu_util import APPEND_LSE_ATOL, assert_attn_close, bits
+from tests.test_gpu_rope import rope_table
 
 pytestmark = pytest.mark.gpu
 SCALE = 1.0 / math.sqrt(128)
@@ -74,3 +75,45 @@ def test_cut_tiles_vs_oracle(device, Hq, Hkv, ctx, T, fp8):
                                      w.append_table(), SCALE)
     assert_attn_close(out.cpu().numpy(), ref, "append line")
     np.testing.assert_allclose(lse.cpu().numpy(), ref_lse, atol=APPEND_LSE_ATOL, rtol=0)
+
+
+@pytest.mark.parametrize("rope", [False, True])
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("Hq,Hkv,ctx,T", [(32, 8, 6000, 70), (8, 1, 3001, 33), (6, 6, 2100, 257)])
+def test_cut_tile_is_the_uncut_tile(device, Hq, Hkv, ctx, T, fp8, rope):
+    """A row alone (its tiles cut) and among so many copies of itself that none is.
+
+    Both round the same weights to bf16 against the same reference, so they differ by
+    the order of fp32 sums over the n <= 6,070 keys: each output and each weight sum is a
+    sum of n terms, off by at most about n 2^-24 of the sum of their magnitudes, in practice
+    sqrt(n) 2^-24 = 5e-6. Weights rounded against another reference differ by 2e-3.
+    """
+    tiles = -(-T // (256 // (Hq // Hkv)))
+    longest, least = -(-(ctx + T) // 64), -(-ctx // 64)
+    copies = 256 * longest // (least * tiles * Hkv) + 1       # a line longer than any cut
+    print(f"[gpu-test] cut tile Hq={Hq} Hkv={Hkv} ctx={ctx} T={T} fp8={fp8} rope={rope}", flush=True)
+    gen = synth.value_generator(19, device)
+    lay = synth.make_layout(np.random.default_rng(19), np.asarray([ctx + T]))
+    scales = (0.02, 0.015) if fp8 else ()
+    make = (lambda s: synth.randn_fp8_codes(s, gen, device, 0.02)) if fp8 else \
+        (lambda s: synth.randn_bf16(s, gen, device))
+    k, v = make((lay.num_pages, Hkv, 16, 128)), make((lay.num_pages, Hkv, 128, 16))
+    q = synth.randn_bf16((T, Hq, 128), gen, device)
+    new = synth.randn_bf16((T, Hkv, 128), gen, device)
+    cs = torch.from_numpy(rope_table(1e6, ctx + T)).to(device) if rope else None
+
+    def call(n):
+        kv = ra.PagedKV(k, v, i32(np.repeat(lay.block_table, n, 0), device), *scales)
+        # every copy writes the same tokens to the same pages
+        return ra.append_write(q.repeat(n, 1, 1), new.repeat(n, 1, 1), new.repeat(n, 1, 1),
+                               i32(np.arange(n + 1) * T, device), i32([ctx] * n, device), kv, T,
+                               ctx + T, SCALE, want_lse=True, cos_sin=cs)
+    one, lse = call(1)
+    many, lse_many = call(copies)
+    torch.cuda.synchronize()
+    whole = many[:T].double()
+    assert torch.equal(many[-T:], many[:T])
+    rel = ((one.double() - whole).norm() / whole.norm()).item()
+    print(f"[parity] cut against uncut: rel_l2={rel:.2e}", flush=True)
+    assert rel <= 2e-5
+    assert (lse - lse_many[:T]).abs().max().item() <= 2e-5
