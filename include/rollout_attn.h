@@ -247,8 +247,10 @@ int rollout_attn_decode_shared_prefix(const void *q, const ra_paged_kv *kv,
  * The work is planned on the device (a one-workgroup kernel orders the rows
  * longest first and queues each KV head's tiles for one XCD, or, with too few
  * tiles to fill the GPU, cuts their key ranges into equal shares whose partial
- * results are merged) and run by one persistent workgroup per CU. Neither the
- * order nor the cuts depend on anything but the rows' lengths.
+ * results are merged) and run by one persistent workgroup per CU. The cuts
+ * depend on the lengths of all the call's rows and their order in the call, and
+ * on nothing else: the same call gives the same bits, while a row's result in
+ * another call (beside other rows) can differ by the order of fp32 sums.
  * Errors as for decode; RA_ERR_UNSUPPORTED also for more than 256 KV heads.
  */
 size_t rollout_attn_append_workspace_size(int32_t B, int32_t Hq, int32_t Hkv,

@@ -49,7 +49,7 @@
 // A decode split is computed as by the decode split kernel but with 8 waves;
 // the decode combine follows as in plain decode. Results do not depend on
 // the order in which entries are taken, and how the append tiles are cut
-// depends on the append rows' lengths alone.
+// depends on the append rows' lengths and places in the call alone.
 #include <atomic>
 
 #include "ra_append_tile.h"
@@ -208,15 +208,6 @@ __global__ __launch_bounds__(kPlanThreads) void mixed_plan_kernel(MixedArgs m, p
     cursor += own[k];
   }
   __syncthreads();
-  for (int b = tid; b < m.B_append; b += kPlanThreads) {
-    const atile::AppendRow r = atile::append_row(m.ap, b);
-    const int nq = row_qblocks(m.ap, r);
-    if (nq == 0) continue;
-    const int nb = atile::append_tile_blocks(m.ap, r, nq - 1);
-    m.order[atomicAdd(&count[min(nb, kCostBuckets) - 1], 1)] = b;
-  }
-  __syncthreads();
-
   // ---- line mode: when a share and what its partial results cost take less
   // than the longest tile
   int shares = 0, share = 0;
@@ -224,6 +215,42 @@ __global__ __launch_bounds__(kPlanThreads) void mixed_plan_kernel(MixedArgs m, p
     shares = (int)min((int64_t)kShares, (line + kMinShare - 1) / kMinShare);
     share = (int)((line + shares - 1) / shares);
     shares = (int)((line + share - 1) / share);
+  }
+
+  // ---- places: the rows of a bucket take them in turn. In line mode, where a row's
+  // place decides how its tiles are cut, rows of one bucket are placed by row number
+  // (a thread counts those before it among the 1,024 of its round); in queue mode the
+  // order only says who starts first.
+  if (shares) {
+    int *const s_bucket = &s_row[0][0];
+    for (int b0 = 0; b0 < m.B_append; b0 += kPlanThreads) {
+      const int b = b0 + tid;
+      int bucket = -1;
+      if (b < m.B_append) {
+        const atile::AppendRow r = atile::append_row(m.ap, b);
+        const int nq = row_qblocks(m.ap, r);
+        if (nq > 0) bucket = min(atile::append_tile_blocks(m.ap, r, nq - 1), kCostBuckets) - 1;
+      }
+      s_bucket[tid] = bucket;
+      __syncthreads();
+      if (bucket >= 0) {
+        int before = 0;
+        for (int i = 0; i < tid; ++i) before += s_bucket[i] == bucket;
+        m.order[count[bucket] + before] = b;
+      }
+      __syncthreads();
+      if (bucket >= 0) atomicAdd(&count[bucket], 1);
+      __syncthreads();
+    }
+  } else {
+    for (int b = tid; b < m.B_append; b += kPlanThreads) {
+      const atile::AppendRow r = atile::append_row(m.ap, b);
+      const int nq = row_qblocks(m.ap, r);
+      if (nq == 0) continue;
+      const int nb = atile::append_tile_blocks(m.ap, r, nq - 1);
+      m.order[atomicAdd(&count[min(nb, kCostBuckets) - 1], 1)] = b;
+    }
+    __syncthreads();
   }
 
   // ---- tiles: rows in the order above, each row's query blocks last first;

@@ -117,3 +117,38 @@ def test_cut_tile_is_the_uncut_tile(device, Hq, Hkv, ctx, T, fp8, rope):
     print(f"[parity] cut against uncut: rel_l2={rel:.2e}", flush=True)
     assert rel <= 2e-5
     assert (lse - lse_many[:T]).abs().max().item() <= 2e-5
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,ctx,T", [(100, 8, 1, 8000, 32), (70, 16, 2, 12800, 20),
+                                            (1100, 4, 1, 1200, 1)])
+def test_many_equal_rows_repeat(device, B, Hq, Hkv, ctx, T):
+    """More equal rows than a wave has lanes, cut: every row keeps its place from call to call.
+
+    Rows of one length share a bucket of the plan's sort; a row's place among them decides
+    where it is cut, so its bits. The last row is long (its tiles make the call one that is
+    cut), the others share its pages and have queries of their own.
+    """
+    print(f"[gpu-test] many equal rows B={B} Hkv={Hkv} ctx={ctx} T={T}", flush=True)
+    gen = synth.value_generator(20, device)
+    long = 64 * (16 + -(-B * Hkv * (ctx // 64 + 1) // 256) + 2) + ctx    # a line shorter than 256 x it
+    lay = synth.make_layout(np.random.default_rng(20), np.asarray([long + T]))
+    k = synth.randn_bf16((lay.num_pages, Hkv, 16, 128), gen, device)
+    v = synth.randn_bf16((lay.num_pages, Hkv, 128, 16), gen, device)
+    kv = ra.PagedKV(k, v, i32(np.repeat(lay.block_table, B, 0), device))
+    q = synth.randn_bf16((B * T, Hq, 128), gen, device)
+    lens = [ctx] * (B - 1) + [long]
+    args = (q, i32(np.arange(B + 1) * T, device), i32(lens, device), kv)
+    out, lse = ra.append(*args, T, long + T, SCALE, want_lse=True)
+    one = ra.PagedKV(k, v, i32(lay.block_table, device))
+    for _ in range(8):
+        again, lse2 = ra.append(*args, T, long + T, SCALE, want_lse=True)
+        _, mixed, _, _ = ra.mixed(q[:1], one, i32([ctx], device), *args, ctx, T, long + T, SCALE)
+        torch.cuda.synchronize()
+        assert torch.equal(out, again) and torch.equal(lse, lse2), "not deterministic"
+        assert torch.equal(out, mixed), "append part of mixed() differs"
+    rows = [0, 1, B // 2, B - 2, B - 1]
+    pick = np.concatenate([np.arange(b * T, (b + 1) * T) for b in rows])
+    sel = bits(q)[pick]
+    ref, _ = oracle.append(sel, np.arange(len(rows) + 1) * T, np.asarray(lens)[rows], bits(k), bits(v),
+                           np.repeat(lay.block_table, len(rows), 0), SCALE)
+    assert_attn_close(out.cpu().numpy()[pick], ref, "many equal rows")
