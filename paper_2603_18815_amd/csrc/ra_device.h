@@ -120,7 +120,7 @@ __device__ __forceinline__ u32x2 quantize8(u32x4 v, float inv_scale) {
   return r;
 }
 
-__device__ __forceinline__ int clamp_page(int id, int num_pages) {
+__host__ __device__ __forceinline__ int clamp_page(int id, int num_pages) {
   return min(max(id, 0), num_pages - 1);
 }
 

@@ -74,7 +74,7 @@ struct WriteItem {
 
 // First page item of row b: a row of n tokens touches at most n / 16 + 2 pages,
 // and floor((x + n) / 16) - floor(x / 16) >= floor(n / 16).
-__device__ __forceinline__ int row_item(const WriteArgs &a, int b) {
+__host__ __device__ __forceinline__ int row_item(const WriteArgs &a, int b) {
   return min(max(a.cu_new[b], 0), a.total_new) / kPage + 2 * b;
 }
 
@@ -83,13 +83,15 @@ inline int64_t write_items(int32_t B, int32_t total_new) {
   return (int64_t)total_new / kPage + 2 * (int64_t)B;
 }
 
-// Row extent clamped so that no access leaves the caller's arrays.
-__device__ __forceinline__ WriteItem write_item(const WriteArgs &a, int chunk, int b) {
+// Row extent clamped so that no access leaves the caller's arrays. chunk < 0 (a page
+// item before the first row's, where cu_new does not start at 0, or of a cu_new that
+// decreases): nothing to write, and no page of the table to look up.
+__host__ __device__ __forceinline__ WriteItem write_item(const WriteArgs &a, int chunk, int b) {
   WriteItem it;
   it.active = false;
   it.cu0 = min(max(a.cu_new[b], 0), a.total_new);
   const int n = min(min(max(a.cu_new[b + 1] - it.cu0, 0), a.max_new), a.total_new - it.cu0);
-  if (n <= 0) return it;
+  if (n <= 0 || chunk < 0) return it;
   it.s = min(max(a.start_pos[b], 0), a.max_pos - n);
   if (it.s < 0) return it;
   it.pg = it.s / kPage + chunk;
