@@ -124,21 +124,31 @@ __host__ __device__ __forceinline__ int clamp_page(int id, int num_pages) {
   return min(max(id, 0), num_pages - 1);
 }
 
-// Largest i in [0, n) with value(i) <= pos, for a non-decreasing value() with
-// value(0) <= pos (0 if there is none); all 64 lanes of a wave call it
-// together (64 probes a round).
+// Rounds of wave_search: count(lo, step, len) says how many of the 64 probes lo,
+// lo + step, ... below lo + len come before or at the position searched. The result lies
+// in [0, n) whatever it says in [0, 64] (a signed count: none is the first row).
+template <typename Count>
+__host__ __device__ __forceinline__ int search_rounds(int n, Count count) {
+  int lo = 0, len = n;
+  while (len > 1) {
+    const int step = (len + kWave - 1) / kWave;
+    const int hits = count(lo, step, len), c = hits > 0 ? hits - 1 : 0;
+    lo += c * step;
+    len = len - c * step < step ? len - c * step : step;
+  }
+  return lo;
+}
+
+// Largest i in [0, n) with value(i) <= pos, for a non-decreasing value() (0 if there is
+// none); all 64 lanes of a wave call it together (64 probes a round).
 template <typename Value>
 __device__ __forceinline__ int wave_search(int n, int pos, Value value) {
   const int lane = threadIdx.x & (kWave - 1);
-  int lo = 0, len = n;
-  while (len > 1) {
-    const int step = (len + kWave - 1) / kWave, off = lane * step;
+  return search_rounds(n, [&](int lo, int step, int len) {
+    const int off = lane * step;
     const bool le = off < len && value(lo + off) <= pos;
-    const int c = max(__popcll(__ballot(le)) - 1, 0);
-    lo += c * step;
-    len = min(step, len - c * step);
-  }
-  return lo;
+    return (int)__popcll(__ballot(le));
+  });
 }
 
 constexpr float kLog2e = 1.4426950408889634f;

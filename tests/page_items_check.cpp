@@ -2,6 +2,7 @@
 // cu_new returns, a page item is inactive or writes a page of that row's block table; and
 // for non-decreasing cu_new, also one that starts past 0, every token has exactly one item.
 #include <cstdio>
+#include <cstdlib>
 #include <random>
 #include <vector>
 
@@ -25,9 +26,25 @@ static void check(const std::vector<int> &cu, const std::vector<int> &start, int
   std::vector<int> covered(total, 0);
   const int64_t items = ra::pwrite::write_items(B, total);
   for (int item = 0; item < items; ++item) {
-    int found = 0;   // the last row whose first item is not past this one, row 0 if there is none
-    for (int b = 0; b < B; ++b)
-      if (ra::pwrite::row_item(a, b) <= item) found = b;
+    // the row the kernel's search finds, its 64 probes a round counted here
+    const int found = ra::search_rounds(B, [&](int lo, int step, int len) {
+      int hits = 0;
+      for (int off = 0; off < 64 * step && off < len; off += step) {
+        if (lo + off < 0 || lo + off >= B) {
+          ++failures;
+          std::printf("probe of row %d of %d\n", lo + off, B);
+          std::exit(1);
+        }
+        hits += ra::pwrite::row_item(a, lo + off) <= item;
+      }
+      return hits;
+    });
+    if (valid) {
+      int last = 0;
+      for (int b = 0; b < B; ++b)
+        if (ra::pwrite::row_item(a, b) <= item) last = b;
+      if (found != last && failures++ < 5) std::printf("item %d: row %d, not %d\n", item, found, last);
+    }
     for (int b = 0; b < B; ++b) {
       const int chunk = item - ra::pwrite::row_item(a, b);
       if (chunk < -kMargin / 2) continue;

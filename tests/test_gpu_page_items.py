@@ -68,3 +68,32 @@ def test_page_write_items_bitexact(device, n, Hkv, fp8, rope):
         kx, vx = oracle.page_write(src, bits(v_new), cu, start, lay.block_table, k0, v0)
     assert np.array_equal(bits(k), kx) and np.array_equal(bits(v), vx), "page write"
     assert np.array_equal(bits(kf), kx) and np.array_equal(bits(vf), vx), "fused write"
+
+
+@pytest.mark.parametrize("first", [5, 40, 300])
+def test_slice_of_a_longer_cu(device, first):
+    """Rows `first`.. of a longer call: cu_new starts past 0, so the first page items lie
+    before its first row. Both writes leave the pools of the same rows written alone."""
+    print(f"[gpu-test] slice of cu from row {first}", flush=True)
+    n = ([1, 17, 0, 33] * 100)[:first] + [1] * 40 + [500, 0, 16]
+    rng = np.random.default_rng(43)
+    start = rng.integers(0, 40, len(n)).astype(np.int32)
+    lay = synth.make_layout(rng, start + np.asarray(n))
+    gen = synth.value_generator(43, device)
+    k, v = synth.randn_bf16((lay.num_pages, 2, 16, 128), gen, device), \
+        synth.randn_bf16((lay.num_pages, 2, 128, 16), gen, device)
+    kf, vf = k.clone(), v.clone()
+    cu = np.concatenate([[0], np.cumsum(n)]).astype(np.int32)
+    k_new = synth.randn_bf16((int(cu[-1]), 2, 128), gen, device)
+    v_new = synth.randn_bf16((int(cu[-1]), 2, 128), gen, device)
+    k0, v0 = bits(k), bits(v)
+    bt, max_pos = lay.block_table[first:], int((start + np.asarray(n))[first:].max())
+    args = (i32(cu[first:], device), i32(start[first:], device))
+    ra.kv_page_write(k_new, v_new, *args, ra.PagedKV(k, v, i32(bt, device)), 500, max_pos)
+    ra.append_write(k_new, k_new, v_new, *args, ra.PagedKV(kf, vf, i32(bt, device)), 500, max_pos)
+    torch.cuda.synchronize()
+    own = slice(int(cu[first]), int(cu[-1]))
+    kx, vx = oracle.page_write(bits(k_new)[own], bits(v_new)[own], cu[first:] - cu[first],
+                               start[first:], bt, k0, v0)
+    assert np.array_equal(bits(k), kx) and np.array_equal(bits(v), vx), "page write"
+    assert np.array_equal(bits(kf), kx) and np.array_equal(bits(vf), vx), "fused write"
