@@ -499,24 +499,43 @@ __global__ __launch_bounds__(kMixThreads, 1) void mixed_kernel(MixedArgs args) {
   }
 }
 
-// Merge of the pieces of the tile that share w starts and does not end (line
-// mode): pieces 2w + 1, 2(w + 1), ..., in this order. Grid (kShares,
-// kMergeParts): a workgroup takes 256 / kMergeParts query rows, 32 lanes each
-// with four dims of a row.
-constexpr int kMergeThreads = 256;
-constexpr int kMergeParts = 32;
+// Merge of the pieces of the cut tiles (line mode): of the tile that share w starts and
+// does not end, pieces 2w + 1, 2(w + 1), ..., in this order. The cut tiles' query rows, 32 at
+// a time (32 lanes each, with four dims of a row), are dealt to kMergeGroups workgroups, few
+// enough that a call in queue mode, which launches them for nothing, loses 2 us (a
+// workgroup for every 8 rows of every share: 3.4 us); 2 rows of 64..512 new tokens over
+// 2k..24k keys take 195 us a call with these, 204 us with those.
+constexpr int kMergeThreads = 1024;
+constexpr int kMergeGroups = 512;
+constexpr int kMergeRows = kMergeThreads / 32;
+constexpr int kMergeParts = atile::kRowsPerGroup / kMergeRows;
 __global__ __launch_bounds__(kMergeThreads) void append_merge_kernel(MixedArgs m) {
-  const int w = blockIdx.x;
-  const int4 cut = m.cut[w];
-  if (cut.w == 0) return;
-  const atile::AppendRow r = atile::append_row(m.ap, cut.x);
-  const int G = m.ap.group, i0 = cut.y * m.ap.q_per_block;
-  const int rows = min(r.T - i0, m.ap.q_per_block) * G;   // query rows of the tile
-  constexpr int kRows = atile::kRowsPerGroup / kMergeParts;
-  const int d = (threadIdx.x & 31) * 4;
-  for (int k = threadIdx.x / 32; k < kRows; k += kMergeThreads / 32) {
-    const int row = blockIdx.y * kRows + k;
-    if (row >= rows) return;
+  if (m.header[kHdrShares] == 0) return;
+  // the shares with a cut tile, in order
+  __shared__ int s_cut[kShares];
+  __shared__ int s_count[kShares / kWave];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const bool is_cut = tid < kShares && m.cut[tid].w > 0;
+  const unsigned long long cut_lanes = __ballot(is_cut);
+  if (tid < kShares && lane == 0) s_count[wave] = (int)__popcll(cut_lanes);
+  __syncthreads();
+  int before = 0, cuts = 0;
+  for (int v = 0; v < kShares / kWave; ++v) {
+    before += v < wave ? s_count[v] : 0;
+    cuts += s_count[v];
+  }
+  if (is_cut) s_cut[before + (int)__popcll(cut_lanes & ((1ull << lane) - 1))] = tid;
+  __syncthreads();
+
+  const int G = m.ap.group, d = (tid & 31) * 4;
+  for (int item = blockIdx.x; item < cuts * kMergeParts; item += kMergeGroups) {
+    const int w = s_cut[item / kMergeParts];
+    const int4 cut = m.cut[w];
+    const atile::AppendRow r = atile::append_row(m.ap, cut.x);
+    const int i0 = cut.y * m.ap.q_per_block;
+    const int rows = min(r.T - i0, m.ap.q_per_block) * G;   // query rows of the tile
+    const int row = item % kMergeParts * kMergeRows + tid / 32;
+    if (row >= rows) continue;
     auto slot = [&](int p) { return (size_t)(2 * (w + p) + (p == 0)) * atile::kRowsPerGroup + row; };
     // eight pieces' loads in flight together
     constexpr int kBatch = 8;
@@ -703,7 +722,7 @@ hipError_t launch_mixed(const uint16_t *q_decode, const PagedKV &kv_decode,
   if ((e = hipGetLastError()) != hipSuccess) return e;
   // (line mode needs a tile of more than kLineCost key blocks)
   if (B_append > 0 && tile_blocks > kLineCost) {
-    hipLaunchKernelGGL(append_merge_kernel, dim3(kShares, kMergeParts), dim3(kMergeThreads), 0,
+    hipLaunchKernelGGL(append_merge_kernel, dim3(kMergeGroups), dim3(kMergeThreads), 0,
                        stream, m);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
