@@ -125,7 +125,7 @@ const char *ra_status_string(int status) {
 size_t rollout_attn_decode_workspace_size(int32_t B, int32_t Hq, int32_t Hkv,
                                           int32_t max_kv_len) {
   if (B <= 0 || Hq <= 0 || Hkv <= 0 || max_kv_len < 0) return 0;
-  return ra::decode_workspace_bytes(B, Hq, ra::decode_plan(B, Hkv, max_kv_len, true));
+  return ra::decode_workspace_bytes(B, Hq, ra::decode_plan(B, Hkv, max_kv_len, Hq / Hkv));
 }
 
 int rollout_attn_decode(const void *q, const ra_paged_kv *kv, const int32_t *kv_lens, int32_t B,
@@ -134,7 +134,7 @@ int rollout_attn_decode(const void *q, const ra_paged_kv *kv, const int32_t *kv_
   const int s = check_decode(q, kv, kv_lens, B, Hq, max_kv_len, scale, out);
   if (s != RA_OK) return s;
   if (B == 0) return RA_OK;
-  ra::DecodePlan plan = ra::decode_plan(B, kv->num_kv_heads, max_kv_len, true);
+  ra::DecodePlan plan = ra::decode_plan(B, kv->num_kv_heads, max_kv_len, Hq / kv->num_kv_heads);
   if (!workspace) return RA_ERR_WORKSPACE;
   while (workspace_bytes < ra::decode_workspace_bytes(B, Hq, plan))
     if (!coarsen_plan(&plan, B, kv->num_kv_heads, max_kv_len)) return RA_ERR_WORKSPACE;
@@ -149,7 +149,7 @@ int rollout_attn_decode_noalloc(const void *q, const ra_paged_kv *kv, const int3
   const int s = check_decode(q, kv, kv_lens, B, Hq, max_kv_len, scale, out);
   if (s != RA_OK) return s;
   if (B == 0) return RA_OK;
-  const ra::DecodePlan plan = ra::decode_plan(B, kv->num_kv_heads, max_kv_len, true);
+  const ra::DecodePlan plan = ra::decode_plan(B, kv->num_kv_heads, max_kv_len, Hq / kv->num_kv_heads);
   if (ra::decode_workspace_bytes(B, Hq, plan) > RA_NOALLOC_SCRATCH_BYTES) return RA_ERR_WORKSPACE;
   void *ws = nullptr;
   const hipError_t e = device_scratch(&ws);
@@ -162,7 +162,7 @@ size_t rollout_attn_decode_shared_prefix_workspace_size(int32_t B, int32_t Hq, i
                                                         int32_t max_kv_len,
                                                         int32_t max_prefix_len) {
   if (B <= 0 || Hq <= 0 || Hkv <= 0 || max_kv_len < 0 || max_prefix_len < 0) return 0;
-  return ra::shared_prefix_workspace_bytes(B, Hq, ra::decode_plan(B, Hkv, max_kv_len, true),
+  return ra::shared_prefix_workspace_bytes(B, Hq, ra::decode_plan(B, Hkv, max_kv_len, Hq / Hkv),
                                            max_prefix_len);
 }
 
@@ -185,7 +185,7 @@ int rollout_attn_decode_shared_prefix(const void *q, const ra_paged_kv *kv,
   if (B == 0) return RA_OK;
   if (num_groups == 0 || max_group_rows == 0 || max_group_rows > B || num_groups > B)
     return RA_ERR_SHAPE;
-  ra::DecodePlan plan = ra::decode_plan(B, kv->num_kv_heads, max_kv_len, true);
+  ra::DecodePlan plan = ra::decode_plan(B, kv->num_kv_heads, max_kv_len, Hq / kv->num_kv_heads);
   for (;;) {
     const ra::SharedPrefixShape sh = ra::shared_prefix_shape(Hq / kv->num_kv_heads, num_groups,
                                                              max_group_rows, plan, max_prefix_len);

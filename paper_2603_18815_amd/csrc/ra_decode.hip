@@ -104,12 +104,17 @@ int64_t split_override() {
 //   256; 1 row of 65,000: 54 and 65 us). The longest row keeps at most
 //   kSmallSlots slots: its combine reads them in rounds (1 row of 30,000 keys, 1
 //   KV head: 17.4 us with 59 slots, 29.4 with 235; 1 row of 8,000, 2 KV heads:
-//   10.2 with 32 slots, 11.1 with 63, 13.2 with 16).
+//   10.2 with 32 slots, 11.1 with 63, 13.2 with 16). Nor are there to be more than
+//   kSmallParts (head, slot) partials, which groups of 17 to 32 heads reach first
+//   (8 rows of 4,000 keys, 32 heads over one KV head, 8,192 partials: 17.2 -> 14.4 us;
+//   16 such rows 18.7 us in 512-key splits, 20.0 in 128-key ones, their shared-prefix
+//   call 21.1 and 30.2; 64 rows of 600 keys, 10,240 partials: 18.1 -> 17.6 us).
 constexpr int kDirectKeys = 512;
 constexpr int kSmallItems = 256;
 constexpr int kSmallSlots = 32;
+constexpr int kSmallParts = 10240;
 
-DecodePlan decode_plan(int32_t B, int32_t hkv, int32_t max_kv_len, bool small) {
+DecodePlan decode_plan(int32_t B, int32_t hkv, int32_t max_kv_len, int32_t group) {
   // Aim for about 8k (row, KV head, split) items on the longest-row bound:
   // enough workgroups to balance rows of different lengths over 256 CUs,
   // long enough splits that the partial results stay well under 1 % of the
@@ -119,9 +124,14 @@ DecodePlan decode_plan(int32_t B, int32_t hkv, int32_t max_kv_len, bool small) {
   int64_t work = (int64_t)B * hkv * (int64_t)(max_kv_len > 0 ? max_kv_len : 1);
   int64_t split = 512;
   while (split < 4096 && work / split > 8192) split *= 2;
-  if (small && max_kv_len > kDirectKeys)
-    while (split > 128 && work / split < kSmallItems && 2 * (int64_t)max_kv_len <= kSmallSlots * split)
+  if (group > 0 && max_kv_len > kDirectKeys) {
+    auto parts = [&](int64_t tokens) {
+      return (int64_t)B * hkv * group * ((max_kv_len + tokens - 1) / tokens);
+    };
+    while (split > 128 && work / split < kSmallItems &&
+           2 * (int64_t)max_kv_len <= kSmallSlots * split && parts(split / 2) <= kSmallParts)
       split /= 2;
+  }
   if (const int64_t forced = split_override()) split = forced;
   DecodePlan p;
   p.split_tokens = (int32_t)split;

@@ -27,9 +27,9 @@ struct DecodePlan {
   int32_t split_tokens;   // tokens per split, a multiple of 128
   int32_t max_splits;     // splits of the longest row
 };
-// small: also the shorter splits that suit the decode kernels' 4-wave
-// workgroups when there are few items.
-DecodePlan decode_plan(int32_t B, int32_t hkv, int32_t max_kv_len, bool small = false);
+// group (query heads per KV head): also the shorter splits that suit the decode
+// kernels' 4-wave workgroups when there are few items; 0: without them.
+DecodePlan decode_plan(int32_t B, int32_t hkv, int32_t max_kv_len, int32_t group = 0);
 size_t decode_workspace_bytes(int32_t B, int32_t hq, const DecodePlan &plan);
 
 hipError_t launch_decode(const uint16_t *q, const PagedKV &kv, const int32_t *kv_lens, int32_t B,

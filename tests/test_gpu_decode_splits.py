@@ -2,7 +2,8 @@
 
 Rows of up to 512 keys are one split whose result is final; longer ones are split
 into at least 128 keys, more finely the fewer rows and KV heads there are, and
-merged one slot per step (up to 8 slots) or one slot per lane (32, 64 and more).
+merged a thread per dim (up to 8 slots a row, and with many rows and heads) or one
+slot per lane in rounds of 64. Each case states the slots that its call plans.
 Each call mixes lengths (empty rows and single keys among them) and is compared
 with the fp64 oracle at the decode tolerance; the same rows as one-row groups
 without a shared prefix must give the same bits.
@@ -21,15 +22,22 @@ from tests.gpu_util import DECODE_LSE_ATOL, assert_attn_close, bits
 pytestmark = pytest.mark.gpu
 SCALE = 1.0 / math.sqrt(128)
 
+# (Hq, Hkv, lengths, slots of the longest row: splits of 128, 256 or 512 keys)
 CASES = [
-    (8, 2, [256, 0, 1, 511, 512, 33]),       # final splits, an empty row
-    (17, 1, [512, 0, 100]),                  # the same in two 16-column tiles
-    (4, 4, [513, 0, 128, 129, 512]),         # 5 slots of 128 keys
-    (8, 1, [1024, 1000, 31]),                # 8 slots: the last small merge
-    (8, 1, [1025, 4000, 4097]),              # 9, 32 and 33 slots
-    (32, 1, [8192, 8193, 0, 5]),             # 64 and 65 slots, two tiles
-    (1, 1, [20000, 17]),                     # 157 slots
-    (32, 8, [16000, 16001]),                 # more heads: longer splits
+    (8, 2, [256, 0, 1, 511, 512, 33], 1),    # final splits, an empty row
+    (17, 1, [512, 0, 100], 1),               # the same in two 16-column tiles
+    (4, 4, [513, 0, 128, 129, 512], 5),
+    (8, 1, [1024, 1000, 31], 8),             # the last small merge
+    (8, 1, [1152, 1025, 1024], 9),           # the first larger one, and a small one beside it
+    (8, 1, [4096, 4000, 1], 32),
+    (8, 1, [1025, 4000, 4097], 17),          # 256-key splits
+    (4, 1, [16896, 16385, 512], 33),         # 512-key splits
+    (32, 1, [8192, 8193, 0, 5], 17),         # two tiles
+    (32, 1, [4000] * 15 + [3999], 16),       # two tiles, more rows: 256 keys where 128 would do
+    (1, 1, [20000, 17], 40),
+    (1, 1, [32769, 32768, 32256], 65),       # a round of 64 slots in the merge, one less, one more
+    (2, 1, [65600, 40], 129),                # a third round
+    (32, 8, [16000, 16001], 32),             # more heads: longer splits
 ]
 
 
@@ -38,8 +46,8 @@ def i32(x, dev):
 
 
 @pytest.mark.parametrize("fp8", [False, True])
-@pytest.mark.parametrize("Hq,Hkv,lens", CASES)
-def test_decode_splits_vs_oracle(device, Hq, Hkv, lens, fp8):
+@pytest.mark.parametrize("Hq,Hkv,lens,slots", CASES)
+def test_decode_splits_vs_oracle(device, Hq, Hkv, lens, slots, fp8):
     print(f"[gpu-test] decode splits Hq={Hq} Hkv={Hkv} lens={lens} fp8={fp8}", flush=True)
     w = synth.decode_workload(23, len(lens), Hq, Hkv, lambda r, n: np.asarray(lens), "splits")
     t = synth.make_tensors(w, device)
@@ -52,6 +60,7 @@ def test_decode_splits_vs_oracle(device, Hq, Hkv, lens, fp8):
     synth.poison_unowned(k, v, w.layout)
     kv = ra.PagedKV(k, v, i32(w.decode_table(), device), *scales)
     kl, mk, B = i32(lens, device), max(lens), len(lens)
+    assert ra.decode_workspace_size(B, Hq, Hkv, mk) == B * Hq * slots * 130 * 4
     out, lse = ra.decode(t.q_decode, kv, kl, mk, SCALE, want_lse=True)
     out2 = torch.empty_like(out)
     ra.decode_noalloc(t.q_decode, kv, kl, mk, out2, SCALE)
