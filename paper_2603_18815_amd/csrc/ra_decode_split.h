@@ -429,58 +429,93 @@ __global__ __launch_bounds__(kThreads) void decode_combine_kernel(DecodeArgs a, 
     if (lse && tid == 0) lse[bh] = (M + __log2f(lsum)) * kLn2;
     return;
   }
-  // quad q of the 32-lane quads sums slots q, q + kQuads, ..., four dims a lane
-  const int quad = tid >> 5;
-  const float *o = a.ws_o + bh * a.slots * kHeadDim + 4 * (tid & 31);
-  constexpr int kBatch = 8;
-  f32x4 ov[kBatch];
-  auto load = [&](int s0) __attribute__((always_inline)) {
+  if constexpr (kThreads == kHeadDim) {
+    // a thread per dim, eight slots at a time
+    const float *o = a.ws_o + bh * a.slots * kHeadDim + tid;
+    float M = -INFINITY, acc = 0.f, lsum = 0.f;
+    for (int s0 = 0; s0 < n; s0 += kFewSlots) {
+      float mv[kFewSlots];
 #pragma unroll
-    for (int j = 0; j < kBatch; ++j)
-      if (s0 + kQuads * j + quad < n)
-        ov[j] = *reinterpret_cast<const f32x4 *>(o + (size_t)slot(s0 + kQuads * j + quad) * kHeadDim);
-  };
-  load(0);   // in flight while the weights are worked out
-  // every wave works out the weights: lane i those of slots i, i + 64, ...
-  __shared__ float s_f[kWave], s_o[kQuads][kHeadDim];
-  float M = -INFINITY;
-  for (int s = lane; s < n; s += kWave) M = fmaxf(M, m[slot(s)]);
+      for (int j = 0; j < kFewSlots; ++j) mv[j] = m[slot(min(s0 + j, n - 1))];
 #pragma unroll
-  for (int off = 1; off < kWave; off *= 2) M = fmaxf(M, __shfl_xor(M, off));
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  float lsum = 0.f;
-  for (int w0 = 0; w0 < n; w0 += kWave) {
-    const int s = w0 + lane;
-    const float f = s < n ? fast_exp2(m[slot(s)] - M) : 0.f;
-    if (s < n) lsum += f * l[slot(s)];
-    if (tid < kWave) s_f[lane] = f;
-    __syncthreads();
-    for (int s0 = w0; s0 < min(n, w0 + kWave); s0 += kQuads * kBatch) {
-      if (s0 > 0) load(s0);
+      for (int j = 0; j < kFewSlots; ++j) M = fmaxf(M, mv[j]);
+    }
+    for (int s0 = 0; s0 < n; s0 += kFewSlots) {
+      float f[kFewSlots], ov[kFewSlots], lv[kFewSlots];
+#pragma unroll
+      for (int j = 0; j < kFewSlots; ++j) {
+        const int k = slot(min(s0 + j, n - 1));
+        ov[j] = o[(size_t)k * kHeadDim];
+        lv[j] = l[k];
+        f[j] = fast_exp2(m[k] - M);
+      }
+#pragma unroll
+      for (int j = 0; j < kFewSlots; ++j) {
+        acc += s0 + j < n ? f[j] * ov[j] : 0.f;
+        lsum += s0 + j < n ? f[j] * lv[j] : 0.f;
+      }
+    }
+    out[bh * kHeadDim + tid] = acc / lsum * a.v_scale;
+    if (lse && tid == 0) lse[bh] = (M + __log2f(lsum)) * kLn2;
+  } else {
+    // quad q of the 32-lane quads sums slots q, q + kQuads, ..., four dims a lane
+    const int quad = tid >> 5;
+    const float *o = a.ws_o + bh * a.slots * kHeadDim + 4 * (tid & 31);
+    constexpr int kBatch = 8;
+    f32x4 ov[kBatch];
+    auto load = [&](int s0) __attribute__((always_inline)) {
 #pragma unroll
       for (int j = 0; j < kBatch; ++j)
-        if (s0 + kQuads * j + quad < n) acc += s_f[s0 - w0 + kQuads * j + quad] * ov[j];
+        if (s0 + kQuads * j + quad < n)
+          ov[j] = *reinterpret_cast<const f32x4 *>(o + (size_t)slot(s0 + kQuads * j + quad) * kHeadDim);
+    };
+    load(0);   // in flight while the weights are worked out
+    // every wave works out the weights: lane i those of slots i, i + 64, ...
+    __shared__ float s_f[kWave], s_o[kQuads][kHeadDim];
+    float M = -INFINITY;
+    for (int s = lane; s < n; s += kWave) M = fmaxf(M, m[slot(s)]);
+#pragma unroll
+    for (int off = 1; off < kWave; off *= 2) M = fmaxf(M, __shfl_xor(M, off));
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    float lsum = 0.f;
+    for (int w0 = 0; w0 < n; w0 += kWave) {
+      const int s = w0 + lane;
+      const float f = s < n ? fast_exp2(m[slot(s)] - M) : 0.f;
+      if (s < n) lsum += f * l[slot(s)];
+      if (tid < kWave) s_f[lane] = f;
+      __syncthreads();
+      for (int s0 = w0; s0 < min(n, w0 + kWave); s0 += kQuads * kBatch) {
+        if (s0 > 0) load(s0);
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j)
+          if (s0 + kQuads * j + quad < n) acc += s_f[s0 - w0 + kQuads * j + quad] * ov[j];
+      }
+      __syncthreads();   // s_f is written again
     }
-    __syncthreads();   // s_f is written again
+#pragma unroll
+    for (int off = 1; off < kWave; off *= 2) lsum += __shfl_xor(lsum, off);
+    *reinterpret_cast<f32x4 *>(&s_o[quad][4 * (tid & 31)]) = acc;
+    __syncthreads();
+    if (tid >= kHeadDim) return;
+    float sum = s_o[0][tid];
+#pragma unroll
+    for (int q = 1; q < kQuads; ++q) sum += s_o[q][tid];
+    out[bh * kHeadDim + tid] = sum / lsum * a.v_scale;
+    if (lse && tid == 0) lse[bh] = (M + __log2f(lsum)) * kLn2;
   }
-#pragma unroll
-  for (int off = 1; off < kWave; off *= 2) lsum += __shfl_xor(lsum, off);
-  *reinterpret_cast<f32x4 *>(&s_o[quad][4 * (tid & 31)]) = acc;
-  __syncthreads();
-  if (tid >= kHeadDim) return;
-  float sum = s_o[0][tid];
-#pragma unroll
-  for (int q = 1; q < kQuads; ++q) sum += s_o[q][tid];
-  out[bh * kHeadDim + tid] = sum / lsum * a.v_scale;
-  if (lse && tid == 0) lse[bh] = (M + __log2f(lsum)) * kLn2;
 }
 
-// Launches the combine for rows_y row slots (grid y). Rows of at most kFewSlots
-// slots take 128 threads (half of a larger workgroup would idle: 19.4 against
-// 20.1 us for the call of a batch of short rows), others 256.
+// Launches the combine for rows_y row slots (grid y). A row's round trips are what a
+// small call waits for: 256 threads, 64 slots a trip. Rows of at most kFewSlots slots take
+// one trip with 128 threads too (half of a larger workgroup would idle: 19.4 against 20.1 us
+// for the call of a batch of short rows), and with more (row, head) pairs than kManyPairs
+// the other pairs fill the wait: 64 rows of 100 keys and 32 heads in a shared-prefix call
+// planned for 4,096 keys 41.0 us with 128 threads, 43.5 us with 256; 64 rows of 4k..32k keys
+// 786 us either way.
+constexpr int64_t kManyPairs = 1024;
 inline void launch_combine(const DecodeArgs &a, unsigned rows_y, float *out, float *lse,
                            hipStream_t stream) {
-  if (a.slots <= kFewSlots)
+  if (a.slots <= kFewSlots || (int64_t)a.hq * rows_y > kManyPairs)
     hipLaunchKernelGGL(decode_combine_kernel<128>, dim3(a.hq, rows_y), dim3(128), 0, stream, a, out,
                        lse);
   else

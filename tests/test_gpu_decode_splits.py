@@ -38,6 +38,8 @@ CASES = [
     (1, 1, [32769, 32768, 32256], 65),       # a round of 64 slots in the merge, one less, one more
     (2, 1, [65600, 40], 129),                # a third round
     (32, 8, [16000, 16001], 32),             # more heads: longer splits
+    # over 1,024 (row, head) pairs: a thread per dim, eight slots at a time
+    (64, 4, [4700, 4097, 4096, 513, 0, 1] * 2 + [1000, 2, 3, 4, 5], 10),
 ]
 
 
