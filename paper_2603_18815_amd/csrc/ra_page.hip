@@ -34,7 +34,7 @@ template <int kHeads, bool kSearch>
 void launch_write(const pwrite::WriteArgs &a, int32_t B, dim3 grid, hipStream_t stream) {
   const dim3 block(pwrite::kItemThreads);
   if (a.fp8 && a.cos_sin)
-    hipLaunchKernelGGL((page_write_kernel<true, true, kHeads, kSearch>), grid, block, 0, stream, a, B);
+    hipLaunchKernelGGL((page_write_kernel<true, true, 1, kSearch>), grid, block, 0, stream, a, B);
   else if (a.cos_sin)
     hipLaunchKernelGGL((page_write_kernel<false, true, kHeads, kSearch>), grid, block, 0, stream, a, B);
   else if (a.fp8)
@@ -51,11 +51,14 @@ void launch_write(const pwrite::WriteArgs &a, int32_t B, dim3 grid, hipStream_t 
 //   128..4,096: 44 us with the full grid (10 per page), 23.3 us by search. The
 //   grid is searched once it would be over four times the items.
 // - Rotated keys: four heads of a page share the cosines and sines, 54 -> 47 us
-//   for 32 chunks of 64..2,048 tokens; one head per workgroup otherwise and for
-//   small calls (64 single tokens: 3.9 us with one head, 5.0 us with four).
+//   for 32 chunks of 64..2,048 tokens into bf16 pools; one head per workgroup otherwise
+//   and for small calls (64 single tokens: 3.9 us with one head, 5.0 us with four; 512
+//   chunks of 16: 20.3 and 22.4 us), counted by the pages that their tokens fill, where
+//   four leave a remainder (9 heads: 29.2 and 30.9 us) and for fp8 pools (8 chunks of
+//   2,048: 21.5 and 21.8 us).
 constexpr int kFullGrid = 4;
 constexpr int kRopeHeads = 4;
-constexpr int64_t kRopeUnits = 8192;   // (page, head) units from which rotated writes share them
+constexpr int64_t kRopeUnits = 8192;   // (full page, head) units from which rotated writes share them
 
 __global__ __launch_bounds__(kThreads) void page_gather_kernel(
     const uint16_t *__restrict__ k_pool, const uint16_t *__restrict__ v_pool,
@@ -132,7 +135,9 @@ hipError_t launch_page_write(const uint16_t *k_new, const uint16_t *v_new, const
   const int64_t counted = pwrite::write_items(B, total_new), row = 1 << 22;   // grid x limit
   const bool search = per_row * B > kFullGrid * counted;
   const int64_t items = search ? counted : per_row * B;
-  const int heads = cos_sin && items * kv.hkv >= kRopeUnits ? kRopeHeads : 1;
+  const bool share = cos_sin && !kv.fp8 && kv.hkv % kRopeHeads == 0 &&
+                     (int64_t)(total_new / kPage) * kv.hkv >= kRopeUnits;
+  const int heads = share ? kRopeHeads : 1;
   const unsigned groups = (kv.hkv + heads - 1) / heads;
   const dim3 grid = search ? dim3((unsigned)(items < row ? items : row), groups,
                                   (unsigned)((items + row - 1) / row))

@@ -121,7 +121,7 @@ __device__ __forceinline__ void write_phase1(const WriteArgs &a, const WriteItem
   u32x4 k[kHeads], partner[kHeads], v[kHeads];
 #pragma unroll
   for (int h = 0; h < kHeads; ++h) {
-    if (g0 + h >= a.hkv) break;
+    if (kHeads > 1 && g0 + h >= a.hkv) break;
     const uint16_t *src = a.k_new + row0 + h * kHeadDim;
     k[h] = load_u32x4(src + ch * 8);
     // rope: this chunk's dims 8 ch + 0..7 pair with chunk ch ^ 8
@@ -136,7 +136,7 @@ __device__ __forceinline__ void write_phase1(const WriteArgs &a, const WriteItem
   }
 #pragma unroll
   for (int h = 0; h < kHeads; ++h) {
-    if (g0 + h >= a.hkv) break;
+    if (kHeads > 1 && g0 + h >= a.hkv) break;
     const size_t dst = (((size_t)it.id * a.hkv + g0 + h) * kPage + slot) * kHeadDim + ch * 8;
     if constexpr (kRope)
       k[h] = __builtin_bit_cast(u32x4, rope8(__builtin_bit_cast(bf16x8, k[h]),
@@ -195,7 +195,7 @@ __device__ __forceinline__ void write_heads(const WriteArgs &a, const WriteItem 
   if (!it.active) return;
 #pragma unroll
   for (int h = 0; h < kHeads; ++h)
-    if (g0 + h < a.hkv) write_phase2<kFp8>(a, it, g0 + h, t, sv[h]);
+    if (kHeads == 1 || g0 + h < a.hkv) write_phase2<kFp8>(a, it, g0 + h, t, sv[h]);
 }
 
 }  // namespace pwrite
