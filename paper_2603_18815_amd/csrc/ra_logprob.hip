@@ -294,7 +294,12 @@ __global__ __launch_bounds__(kLpThreads, 2) void logprob_partial_kernel(LogprobA
 // logical chunk c at slot c ^ ((r / 4) % 4), so that 16 lanes reading 16 rows
 // at one logical chunk hit 16 distinct bank groups. A load instruction fills
 // 16 rows: lane l fetches row 16 j + l / 4, the logical chunk stored at slot
-// l % 4. The 32 dims of a step split over the two products as lanes 0-31 dims
+// l % 4.
+// From the packed copy W keeps that copy's order instead: a 32-row tile is chunk 0 of its
+// rows, then chunk 1, ...; a load instruction takes 512 contiguous bytes twice, where
+// the row order took 16 bytes from each of 64 places (2,048 tokens 1,992 -> 1,936 us, 512
+// tokens 594 -> 541 us, 257 tokens over 20,000 rows 81 -> 70 us).
+// The 32 dims of a step split over the two products as lanes 0-31 dims
 // 8 u + 0..7 and lanes 32-63 dims 16 + 8 u + 0..7 (logical chunk 2 half + u).
 constexpr int kTileRows = 256;        // tokens per workgroup
 constexpr int kTileRowsA = 384;       // vocabulary rows per workgroup
@@ -372,13 +377,17 @@ __device__ __forceinline__ void logprob_tile(const LogprobArgs &a, int v0, int t
   const int vlast = kPacked ? (a.V + kPackRows - 1) / kPackRows * kPackRows - 1 : a.V - 1;
 #pragma unroll
   for (int k = 0; k < kLoadsA; ++k) {
-    const int r = 16 * (kLoadsA * wave + k) + lane / 4;
-    const int lc = (lane % 4) ^ ((r >> 2) & 3);
-    const int v = RT == 3 && kPacked ? v0 + r : min(v0 + r, vlast);
-    // packed: 16-byte unit ((s / 2 * tiles + tile) * 4 + lc) * 64 + 32 (s % 2) + v % 32
-    // (the part that depends on the step s is added per step)
-    ga[k] = kPacked ? a.W + ((size_t)(v / 32) * 4 + lc) * kWave * 8 + (v % 32) * 8
-                    : a.W + (size_t)v * a.D + 8 * lc;
+    const int j = kLoadsA * wave + k;
+    if constexpr (kPacked) {
+      // half a 32-row tile, chunks 2 (j % 2) and + 1 of every row: 16-byte units
+      // ((s / 2 * tiles + tile) * 4 + lc) * 64 + 32 (s % 2) + row, 512 contiguous
+      // bytes a chunk (the part that depends on the step s is added per step)
+      const int tile = min(v0 / 32 + j / 2, vlast / 32), lc = 2 * (j & 1) + lane / 32;
+      ga[k] = a.W + ((size_t)tile * 4 + lc) * kWave * 8 + (lane % 32) * 8;
+    } else {
+      const int r = 16 * j + lane / 4, lc = (lane % 4) ^ ((r >> 2) & 3);
+      ga[k] = a.W + (size_t)min(v0 + r, vlast) * a.D + 8 * lc;
+    }
   }
   const int nsteps = a.D / kTileDims;
   auto h_instr = [&](int k) __attribute__((always_inline)) {
@@ -420,7 +429,8 @@ __device__ __forceinline__ void logprob_tile(const LogprobArgs &a, int v0, int t
   const int col = lane & 31, half = lane >> 5;
   const int wv = wave & 3, wt = wave >> 2;
   const int swz = (col >> 2) & 3;   // slot swizzle of every operand row (rows differ from col by multiples of 32)
-  const int rowA = (32 * RT * wv + col) * kTileDims, rowB = (32 * TT * wt + col) * kTileDims;
+  const int rowA = 32 * RT * wv * kTileDims + (kPacked ? 8 * col : kTileDims * col);
+  const int rowB = (32 * TT * wt + col) * kTileDims;
   f32x16 acc[RT][TT];
 #pragma unroll
   for (int i = 0; i < RT; ++i)
@@ -443,7 +453,8 @@ __device__ __forceinline__ void logprob_tile(const LogprobArgs &a, int v0, int t
       const int c = 8 * ((2 * half + u) ^ swz);
       bf16x8 av[RT], bv[TT];
 #pragma unroll
-      for (int i = 0; i < RT; ++i) av[i] = lds16(A + rowA + c + 32 * kTileDims * i);
+      for (int i = 0; i < RT; ++i)
+        av[i] = lds16(A + rowA + (kPacked ? 32 * 8 * (2 * half + u) : c) + 32 * kTileDims * i);
 #pragma unroll
       for (int j = 0; j < TT; ++j) bv[j] = lds16(B + rowB + c + 32 * kTileDims * j);
 #pragma unroll
