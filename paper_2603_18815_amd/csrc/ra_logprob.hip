@@ -538,8 +538,8 @@ __device__ __forceinline__ void logprob_tile(const LogprobArgs &a, int v0, int t
 template <bool kPacked, int TT>
 __global__ __launch_bounds__(kTileThreads, 1) void logprob_tile_kernel(LogprobArgs a) {
   __shared__ TileLds lds;
-  const int whole = TT == 4 ? 0x7fffffff : a.tall * a.token_blocks;
-  const bool split = (int)blockIdx.x >= whole;
+  const int whole = a.tall * a.token_blocks;
+  const bool split = TT != 4 && (int)blockIdx.x >= whole;   // (256-token tiles: none are cut)
   const int id = blockIdx.x - (split ? whole : 0), parts = split ? 4 / TT : 1;
   const int xcd = id % kXcds, slot = id / kXcds, per = a.token_blocks * parts;
   const int chunk = (split ? a.tall : 0) + (slot / per) * kXcds + xcd;
@@ -547,7 +547,7 @@ __global__ __launch_bounds__(kTileThreads, 1) void logprob_tile_kernel(LogprobAr
   if (chunk >= a.chunks) return;
   if (!split)
     logprob_tile<kPacked, true, 3, 4>(a, chunk * kTileRowsA, s, 0, chunk, lds);
-  else
+  else if constexpr (TT != 4)
     logprob_tile<kPacked, true, 3, TT>(a, chunk * kTileRowsA, s / parts, s % parts, chunk, lds);
 }
 
