@@ -72,6 +72,7 @@ constexpr int kHPitch = kDimStep + 8;         // LDS row pitch of the h slice (e
 constexpr int kRoundsMinN = 128;              // larger batches below kTileMinN: tiles of two heights
 constexpr int kTileCus = 256;                 // compute units of an MI355X, one tile each
 constexpr int kTileMinN = 512;                // batches from this size use the 384 x 256 tiles
+constexpr int64_t kMemorySideCache = 256 << 20;   // bytes
 constexpr int kPackRows = 384;                // the packed copy covers V rounded up to this
 // s_waitcnt immediates: vmcnt(0), export and LDS counters not waited on
 constexpr int kWaitVm0 = 0x0F70;
@@ -569,18 +570,20 @@ __global__ __launch_bounds__(kTileThreads, 1) void logprob_rounds_kernel(Logprob
 
 // ---- small batches over a row-major W: one pass of W through LDS ----
 //
-// kWaves waves, each with 32 vocabulary rows and all (up to 32 T) tokens. The
+// kWaves waves, each with 32 vocabulary rows and a block of 32 T tokens. The
 // loop walks D in steps of 64 dims through a ring of kStages LDS stages, refilled
 // kStages - 1 steps ahead by direct global-to-LDS loads of eight rows x 128
 // bytes: whole cache lines, where operand loads straight into registers take
 // each line 16 bytes at a time (a lane needs 16 bytes of its own row).
 // Products, their order and the partial results are those of
-// logprob_partial_kernel.
+// logprob_partial_kernel. kNt: W is marked nontemporal, for heads that the 256 MB
+// memory-side cache cannot hold between calls (64 tokens at 151,936 x 4,096 264 -> 242
+// us); one that fits stays there (at 32,000 x 4,096 58 us nontemporal, 43 us not).
 //
 // Stage layout: row r holds its 64 dims as eight 16-byte chunks, logical chunk c
 // at slot c ^ ((r / 2) % 8), so that 16 lanes reading 16 rows at one logical
 // chunk hit 16 distinct bank groups.
-template <int T, int kWaves, int kStages>
+template <int T, int kWaves, int kStages, bool kNt>
 __global__ __launch_bounds__(kWaves *kWave, 1) void logprob_stream_kernel(LogprobArgs a) {
   constexpr int kTokens = 32 * T, kRows = 32 * kWaves;
   constexpr int kLoadsW = 4, kLoadsH = kTokens / 8 / kWaves;   // per wave and step
@@ -593,7 +596,13 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void logprob_stream_kernel(Logpro
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int col = lane & 31, half = lane >> 5;
-  const int v0 = (blockIdx.x * kWaves + wave) * 32;   // first vocabulary row of this wave
+  // the token blocks of one stretch of the vocabulary on one XCD, as in logprob_partial_kernel
+  constexpr int kChunks = kWaves / kLpWaves;   // 128-row chunks of a workgroup
+  const int id = blockIdx.x, xcd = id % kXcds, slot = id / kXcds;
+  const int block = (slot / a.token_blocks) * kXcds + xcd;
+  const int t0 = (slot - (slot / a.token_blocks) * a.token_blocks) * kTokens;
+  if (block * kChunks >= a.chunks) return;
+  const int v0 = (block * kWaves + wave) * 32;   // first vocabulary row of this wave
 
   const uint16_t *gw[kLoadsW], *gh[kLoadsH];
 #pragma unroll
@@ -604,13 +613,14 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void logprob_stream_kernel(Logpro
 #pragma unroll
   for (int k = 0; k < kLoadsH; ++k) {
     const int r = 8 * (kLoadsH * wave + k) + lane / 8, lc = (lane % 8) ^ ((r >> 1) & 7);
-    gh[k] = a.h + (size_t)min(r, a.N - 1) * a.D + 8 * lc;
+    gh[k] = a.h + (size_t)min(t0 + r, a.N - 1) * a.D + 8 * lc;
   }
   const int nsteps = a.D / kDimStep, last = nsteps - 1;
   auto load = [&](int st, int s) __attribute__((always_inline)) {
 #pragma unroll
     for (int k = 0; k < kLoadsW; ++k)
-      load_lds16_stream(gw[k] + (size_t)s * kDimStep, lds_address(sW[st]) + (4 * wave + k) * 1024u);
+      (kNt ? load_lds16_stream : load_lds16)(gw[k] + (size_t)s * kDimStep,
+                                             lds_address(sW[st]) + (4 * wave + k) * 1024u);
 #pragma unroll
     for (int k = 0; k < kLoadsH; ++k)
       load_lds16(gh[k] + (size_t)s * kDimStep, lds_address(sH[st]) + (kLoadsH * wave + k) * 1024u);
@@ -655,7 +665,7 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void logprob_stream_kernel(Logpro
 #pragma unroll
   for (int tt = 0; tt < T; ++tt) {
     float m, sum;
-    tile_max_sum(a, acc[tt], v0, 32 * tt + col, half, &m, &sum);
+    tile_max_sum(a, acc[tt], v0, t0 + 32 * tt + col, half, &m, &sum);
     if (half == 0) {
       s_m[wave][32 * tt + col] = m;
       s_l[wave][32 * tt + col] = sum;
@@ -663,10 +673,10 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void logprob_stream_kernel(Logpro
   }
   __syncthreads();
   // merge four waves (128 rows) into a partial: one thread per token and chunk
-  for (int i = threadIdx.x; i < kTokens * (kWaves / kLpWaves); i += kWaves * kWave) {
-    const int c = i % kTokens, g = i / kTokens, chunk = blockIdx.x * (kWaves / kLpWaves) + g;
-    if (c < a.N && chunk < a.chunks)
-      merge_waves(a, &s_m[g * kLpWaves], &s_l[g * kLpWaves], c, c, chunk);
+  for (int i = threadIdx.x; i < kTokens * kChunks; i += kWaves * kWave) {
+    const int c = i % kTokens, g = i / kTokens, chunk = block * kChunks + g;
+    if (t0 + c < a.N && chunk < a.chunks)
+      merge_waves(a, &s_m[g * kLpWaves], &s_l[g * kLpWaves], c, t0 + c, chunk);
   }
 }
 
@@ -778,8 +788,9 @@ LastRound logprob_last_round(int32_t token_blocks, int32_t chunks) {
   r.groups = rest == 0 || rest > kTileCus / 2 ? 4 : rest > kTileCus / 4 ? 2 : 1;
   return r;
 }
-bool logprob_in_rounds(int32_t N) { return N > kRoundsMinN && N < kTileMinN; }
 int32_t token_blocks_of(int32_t N) { return (N + kTileRows - 1) / kTileRows; }
+bool logprob_in_squares(int32_t N, int32_t) { return N <= kRoundsMinN; }
+bool logprob_in_rounds(int32_t N, int32_t V) { return N < kTileMinN && !logprob_in_squares(N, V); }
 // 64-token groups of a token block (3 or 4)
 int rounds_groups(int32_t N) {
   const int blocks = token_blocks_of(N);
@@ -788,7 +799,7 @@ int rounds_groups(int32_t N) {
 }  // namespace
 
 int32_t logprob_chunks(int32_t N, int32_t V) {
-  if (logprob_in_rounds(N)) {
+  if (logprob_in_rounds(N, V)) {
     const Rounds r = logprob_rounds(token_blocks_of(N), V);
     return r.tall + r.rest;
   }
@@ -832,15 +843,15 @@ size_t logprob_workspace_bytes(int32_t N, int32_t V, int32_t D) {
 namespace {
 int logprob_tiles(int32_t N) { return N <= 64 ? 2 : kMaxTiles; }
 // tokens per workgroup
-int logprob_token_block(int32_t N) {
-  if (logprob_in_rounds(N)) return 64 * rounds_groups(N);
+int logprob_token_block(int32_t N, int32_t V) {
+  if (logprob_in_rounds(N, V)) return 64 * rounds_groups(N);
   return N >= kTileMinN ? kTileRows : 32 * logprob_tiles(N);
 }
 }  // namespace
 
 int64_t logprob_grid(int32_t N, int32_t V) {
   const int64_t chunks_pad = (logprob_chunks(N, V) + kXcds - 1) / kXcds * kXcds;
-  const int block = logprob_token_block(N);
+  const int block = logprob_token_block(N, V);
   return chunks_pad * ((N + block - 1) / block);
 }
 
@@ -857,7 +868,8 @@ hipError_t launch_logprob(const uint16_t *h, const uint16_t *W, const int32_t *t
   a.D = D;
   a.chunks = logprob_chunks(N, V);
   const int tiles = logprob_tiles(N);
-  a.token_blocks = (N + logprob_token_block(N) - 1) / logprob_token_block(N);
+  const int block = logprob_token_block(N, V);
+  a.token_blocks = (N + block - 1) / block;
   a.ws_m = static_cast<float *>(workspace);
   a.ws_l = a.ws_m + (size_t)N * a.chunks;
   a.tgt = a.ws_l + (size_t)N * a.chunks;
@@ -876,7 +888,7 @@ hipError_t launch_logprob(const uint16_t *h, const uint16_t *W, const int32_t *t
     if (e != hipSuccess) return e;
   }
   a.tall = 0;
-  if (logprob_in_rounds(N)) {
+  if (logprob_in_rounds(N, V)) {
     const Rounds r = logprob_rounds(a.token_blocks, V);
     a.tall = r.tall;
     const int variant = (packed ? 6 : 0) + (rounds_groups(N) == 4 ? 3 : 0) + r.rt - 1;
@@ -924,12 +936,29 @@ hipError_t launch_logprob(const uint16_t *h, const uint16_t *W, const int32_t *t
     hipLaunchKernelGGL((logprob_partial_kernel<2>), grid, dim3(kLpThreads), 0, stream, a);
   else if (packed)
     hipLaunchKernelGGL((logprob_partial_kernel<kMaxTiles>), grid, dim3(kLpThreads), 0, stream, a);
-  else if (tiles == 2)   // two workgroups per compute unit (72 KB of LDS each)
-    hipLaunchKernelGGL((logprob_stream_kernel<2, 4, 3>), dim3(a.chunks), dim3(4 * kWave), 0, stream,
-                       a);
-  else
-    hipLaunchKernelGGL((logprob_stream_kernel<kMaxTiles, 8, 3>), dim3((a.chunks + 1) / 2),
-                       dim3(8 * kWave), 0, stream, a);
+  else {
+    // Row-major. 64 tokens: 72 KB of LDS, two workgroups per compute unit. More: workgroups
+    // of 4 waves while those of 8 would leave compute units idle (at most 256 chunks:
+    // 128 tokens at 32,000 x 4,096 72 us with 8 waves, 50 us with 4).
+    const bool nt = (int64_t)V * D * (int64_t)sizeof(uint16_t) > kMemorySideCache;
+    const int waves = tiles == 2 || a.chunks <= kTileCus ? 4 : 8;
+    const dim3 g(waves == 4 ? grid.x : (unsigned)((a.chunks + 1) / 2 + kXcds - 1) / kXcds * kXcds);
+    const dim3 b(waves * kWave);
+    const int variant = (tiles == 2 ? 0 : waves) | (nt ? 1 : 0);
+    switch (variant) {
+#define RA_STREAM(X, T, W, NT)                                                        \
+  case X:                                                                             \
+    hipLaunchKernelGGL((logprob_stream_kernel<T, W, 3, NT>), g, b, 0, stream, a);     \
+    break;
+      RA_STREAM(0, 2, 4, false)
+      RA_STREAM(1, 2, 4, true)
+      RA_STREAM(4, kMaxTiles, 4, false)
+      RA_STREAM(5, kMaxTiles, 4, true)
+      RA_STREAM(8, kMaxTiles, 8, false)
+      RA_STREAM(9, kMaxTiles, 8, true)
+#undef RA_STREAM
+    }
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(logprob_combine_kernel, dim3((unsigned)N), dim3(kLpThreads), 0, stream, a,

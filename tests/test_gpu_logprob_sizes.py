@@ -21,6 +21,8 @@ pytestmark = pytest.mark.gpu
 SIZES = [
     # N <= 128: fewer steps than the LDS ring's stages, ragged chunks, tokens at a tile's edges
     (1, 130, 64), (64, 257, 128), (65, 500, 192), (128, 1025, 320), (33, 127, 448),
+    # the same over 256 chunks of 128 rows, the last of 4-wave workgroups, and the next
+    (70, 32768, 64), (128, 32769, 128),
     # 129 <= N < 512 with fewer rows than one round of tiles: one height only
     (129, 1000, 192), (192, 70000, 64), (193, 98304, 64),
     # one full round of 384-row chunks, then chunks of 128, 256 and 384 rows
