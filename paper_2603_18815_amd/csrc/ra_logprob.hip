@@ -14,7 +14,9 @@
 //   LDS in whole cache lines; bound by HBM reading 128-byte pieces 8 KB apart
 //   (64 tokens 279 -> 241 us, 128 tokens 339 -> 304 us; one 8-wave workgroup
 //   per compute unit instead of two of 4 waves: 285 us at 64 tokens).
-// - 128 < N < 512: logprob_rounds_kernel. 256-token tiles, 384 vocabulary rows
+// - 128 < N < 512 over a small vocabulary: the two above, a block of 128 tokens a
+//   workgroup (logprob_in_squares).
+// - 128 < N < 512 otherwise: logprob_rounds_kernel. 256-token tiles, 384 vocabulary rows
 //   high while they fill the 256 compute units, then lower ones for what is
 //   left, so that the last round is short (row-major 129 tokens 464 -> 287 us,
 //   256 526 -> 329, 257 658 -> 470, 400 814 -> 554, 511 870 -> 575; packed 129
@@ -789,7 +791,18 @@ LastRound logprob_last_round(int32_t token_blocks, int32_t chunks) {
   return r;
 }
 int32_t token_blocks_of(int32_t N) { return (N + kTileRows - 1) / kTileRows; }
-bool logprob_in_squares(int32_t N, int32_t) { return N <= kRoundsMinN; }
+// Batches of few tiles: 128 x 128, when all of them run at once, one a compute unit, and
+// the blocks of 192 or 256 tokens are fuller than kSquareTokens on average. Then a step's
+// chain is what a tile takes, and the smaller tile's is shorter (4,096 x 4,096, row-major:
+// 256 tokens 55 us in tiles of 256 tokens, 43 us in squares, 384 tokens 54 and 43 us; packed
+// 52 and 46 us, 46 and 46 us); emptier blocks are no slower than squares (257 tokens 45 and
+// 44 us, packed 45 and 47 us).
+constexpr int kSquareTokens = 140;
+bool logprob_in_squares(int32_t N, int32_t V) {
+  if (N <= kRoundsMinN) return true;
+  return N < kTileMinN && N > kSquareTokens * token_blocks_of(N) &&
+         ((int64_t)V + 127) / 128 * ((N + 127) / 128) <= kTileCus;
+}
 bool logprob_in_rounds(int32_t N, int32_t V) { return N < kTileMinN && !logprob_in_squares(N, V); }
 // 64-token groups of a token block (3 or 4)
 int rounds_groups(int32_t N) {

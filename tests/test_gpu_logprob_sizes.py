@@ -1,7 +1,7 @@
 """Token log-probabilities at the sizes where the kernel or the cut of the vocabulary changes.
 
 Up to 128 tokens a row-major head goes through LDS (4 or 8 waves, 64 or 128
-tokens); from 129 to 511 tokens tiles of 384 vocabulary rows fill the 256 compute
+tokens), and so do more tokens over few rows; from 129 to 511 tokens tiles of 384 vocabulary rows fill the 256 compute
 units and lower ones (128, 256 or 384 rows) take the rest, in one or two blocks of
 up to 192 or 256 tokens; from 512 tokens the last round's tiles may be cut along
 the tokens. Every case is compared with the fp64 oracle (tolerance as
@@ -23,6 +23,9 @@ SIZES = [
     (1, 130, 64), (64, 257, 128), (65, 500, 192), (128, 1025, 320), (33, 127, 448),
     # the same over 256 chunks of 128 rows, the last of 4-wave workgroups, and the next
     (70, 32768, 64), (128, 32769, 128),
+    # 129 <= N < 512, few rows: 128 x 128 tiles in two, three and four blocks of tokens
+    (141, 1000, 192), (256, 16384, 64), (301, 700, 128), (384, 10880, 64), (500, 8192, 448),
+    (256, 16385, 64),                       # and tiles of 192 or 256 tokens from there on
     # 129 <= N < 512 with fewer rows than one round of tiles: one height only
     (129, 1000, 192), (192, 70000, 64), (193, 98304, 64),
     # one full round of 384-row chunks, then chunks of 128, 256 and 384 rows
