@@ -263,8 +263,10 @@ int append_write_impl(const void *q, const void *k_new, const void *v_new, const
   const ra::MixedLayout layout = ra::mixed_layout(0, B, Hq, k.hkv, k.hkv, 0, max_q_len);
   if (layout.max_tiles > 0x7fffffff - 0xffff || layout.qblocks >= (1 << 23))
     return RA_ERR_UNSUPPORTED;
-  // the write runs as (row, page, head) blocks, four per workgroup
-  if ((int64_t)B * k.hkv * ((int64_t)max_q_len / RA_PAGE_SIZE + 2) / 4 > 0x7ffffff0)
+  // the write's grid (its workgroups beside the planning one), and the limit that calls
+  // have had: four (row, page, head) blocks at the longest chunk's pages a workgroup
+  if (ra::fused_write_blocks(B, total_q, k.hkv) > 0x7ffffff0 ||
+      (int64_t)B * k.hkv * ((int64_t)max_q_len / RA_PAGE_SIZE + 2) / 4 > 0x7ffffff0)
     return RA_ERR_UNSUPPORTED;
   if (!workspace || workspace_bytes < layout.bytes) return RA_ERR_WORKSPACE;
   return hip_status(ra::launch_mixed(

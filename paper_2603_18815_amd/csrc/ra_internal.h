@@ -75,6 +75,8 @@ struct MixedLayout {
 MixedLayout mixed_layout(int32_t B_decode, int32_t B_append, int32_t hq, int32_t hkv_decode,
                          int32_t hkv_append, int32_t max_kv_len_decode, int32_t max_q_len);
 int32_t mixed_hkv_limit();   // KV heads an entry can name
+// Workgroups of the page write fused into an append call.
+int64_t fused_write_blocks(int32_t B, int32_t total_q, int32_t hkv);
 hipError_t launch_mixed(const uint16_t *q_decode, const PagedKV &kv_decode,
                         const int32_t *kv_lens, int32_t B_decode, int32_t max_kv_len_decode,
                         float *out_decode, float *lse_decode, const uint16_t *q_append,

@@ -630,6 +630,17 @@ MixedLayout mixed_layout(int32_t B_decode, int32_t B_append, int32_t hq, int32_t
 
 int32_t mixed_hkv_limit() { return 1 << kHeadBits; }
 
+namespace {
+constexpr int64_t kUnitsPer = kPlanThreads / pwrite::kItemThreads;
+int64_t fused_write_units(int32_t B, int32_t total_q, int32_t hkv) {
+  return pwrite::write_items(B, total_q) * ((hkv + kFusedHeads - 1) / kFusedHeads);
+}
+}  // namespace
+
+int64_t fused_write_blocks(int32_t B, int32_t total_q, int32_t hkv) {
+  return (fused_write_units(B, total_q, hkv) + kUnitsPer - 1) / kUnitsPer;
+}
+
 hipError_t launch_mixed(const uint16_t *q_decode, const PagedKV &kv_decode,
                         const int32_t *kv_lens, int32_t B_decode, int32_t max_kv_len_decode,
                         float *out_decode, float *lse_decode, const uint16_t *q_append,
@@ -662,11 +673,7 @@ hipError_t launch_mixed(const uint16_t *q_decode, const PagedKV &kv_decode,
   // the fused page write (append rows only): the chunks' tokens at ctx_lens
   const pwrite::WriteArgs w = pwrite::write_args(k_new, v_new, cu_q, ctx_lens, kv_append, total_q,
                                                  max_q_len, max_kv_len_append, cos_sin, rope_rows);
-  const int64_t write_units =
-      k_new ? pwrite::write_items(B_append, total_q) *
-                  ((kv_append.hkv + kFusedHeads - 1) / kFusedHeads)
-            : 0;
-  constexpr int64_t kUnitsPer = kPlanThreads / pwrite::kItemThreads;
+  const int64_t write_units = k_new ? fused_write_units(B_append, total_q, kv_append.hkv) : 0;
   const int64_t write_blocks = (write_units + kUnitsPer - 1) / kUnitsPer;
   hipLaunchKernelGGL(mixed_plan_kernel, dim3((unsigned)(1 + write_blocks)), dim3(kPlanThreads), 0,
                      stream, m, w, write_units);

@@ -474,3 +474,15 @@ def test_microbench_exports_and_validation():
     assert lib.ra_mb_mfma_bf16(None, 1, 1, FAKE, FAKE, None) == 1
     assert lib.ra_mb_mfma_bf16(FAKE, 0, 1, FAKE, FAKE, None) == 2
     assert lib.ra_mb_lds_read(1, 0, FAKE, FAKE, None) == 2
+
+
+def test_append_write_grid_limit(lib):
+    """The fused write's grid (pages counted by tokens, two KV heads each, four a workgroup)
+    is bounded before the workspace is looked at; a call within it asks for workspace."""
+    def call(total_q, hkv):
+        kv = _kv(num_kv_heads=hkv, bt_stride=1 << 20, num_pages=1 << 20)
+        return lib.rollout_attn_append_write(FAKE, FAKE, FAKE, FAKE, FAKE, ctypes.byref(kv), 2, hkv,
+                                             total_q, 16, 64, 0.1, FAKE, None, FAKE, 16, None)
+    assert call(2**31 - 1, 256) == _lib.RA_ERR_UNSUPPORTED    # 4.3e9 workgroups
+    assert call(2**31 - 1, 64) == _lib.RA_ERR_WORKSPACE
+    assert call(64, 256) == _lib.RA_ERR_WORKSPACE
