@@ -241,8 +241,10 @@ int rollout_attn_decode_shared_prefix(const void *q, const ra_paged_kv *kv,
  *   lse         fp32 [total_q][Hq] or NULL
  *   workspace   device scratch of at least
  *               rollout_attn_append_workspace_size(B, Hq, Hkv, max_q_len) bytes
- *               (the call's work lists, counters and partial results, some 68
- *               MB, rewritten by every call; contents on entry are ignored).
+ *               (the call's work lists, counters and partial results, up to
+ *               some 68 MB of them, less for chunks of fewer tokens than a
+ *               tile's 256 / (Hq / Hkv); rewritten by every call; contents on
+ *               entry are ignored).
  *               Calls that share a workspace must not overlap.
  * The work is planned on the device (a one-workgroup kernel orders the rows
  * longest first and queues each KV head's tiles for one XCD, or, with too few

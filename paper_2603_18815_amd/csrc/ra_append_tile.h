@@ -150,8 +150,9 @@ __device__ __forceinline__ AppendTile make_tile(const AppendArgs &a, const Appen
 // normalisation and (running max, sum) per query row. A row with no key in the
 // piece has sum 0 and max -inf.
 struct PartialOut {
-  float *o;     // [slot][256 query rows][128]
-  float2 *ml;   // [slot][256 query rows]
+  float *o;     // [slot][rows][128]
+  float2 *ml;   // [slot][rows]
+  int64_t rows; // query rows of the call's fullest tile
 };
 
 // One tile, or a piece of it: KV head g, key blocks [kb0, kb1), by a workgroup
@@ -520,7 +521,7 @@ __device__ __forceinline__ void append_tile(const AppendArgs &a, const AppendTil
   float inv = (kFp8 ? a.v_scale : 1.f) / l;
   float *dst;
   if (slot >= 0) {
-    const size_t prow = (size_t)slot * kRowsPerGroup + r_e;
+    const size_t prow = slot * part.rows + r_e;
     dst = part.o + prow * kHeadDim;
     inv = 1.f;
     if (grp_e == 0) part.ml[prow] = make_float2(l > 0.f ? m_run : -INFINITY, l);

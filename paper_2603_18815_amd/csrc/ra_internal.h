@@ -71,6 +71,7 @@ struct MixedLayout {
   int64_t max_splits;         // bound on decode split entries
   size_t order_offset, tiles_offset, starts_offset, splits_offset, partials_offset;
   size_t pieces_offset, bytes;
+  int32_t piece_rows;         // query rows of a piece of a cut tile
 };
 MixedLayout mixed_layout(int32_t B_decode, int32_t B_append, int32_t hq, int32_t hkv_decode,
                          int32_t hkv_append, int32_t max_kv_len_decode, int32_t max_q_len);

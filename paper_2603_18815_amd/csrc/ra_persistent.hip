@@ -536,7 +536,7 @@ __global__ __launch_bounds__(kMergeThreads) void append_merge_kernel(MixedArgs m
     const int rows = min(r.T - i0, m.ap.q_per_block) * G;   // query rows of the tile
     const int row = item % kMergeParts * kMergeRows + tid / 32;
     if (row >= rows) continue;
-    auto slot = [&](int p) { return (size_t)(2 * (w + p) + (p == 0)) * atile::kRowsPerGroup + row; };
+    auto slot = [&](int p) { return (2 * (w + p) + (p == 0)) * (size_t)m.part.rows + row; };
     // eight pieces' loads in flight together
     constexpr int kBatch = 8;
     float M = -INFINITY;
@@ -609,8 +609,11 @@ MixedLayout mixed_layout(int32_t B_decode, int32_t B_append, int32_t hq, int32_t
   l.qblocks = max_q_len > 0 ? (int32_t)(((int64_t)max_q_len + qpb - 1) / qpb) : 0;
   l.max_tiles = (int64_t)B_append * l.qblocks * hkv_append;
   l.max_splits = (int64_t)B_decode * l.plan.max_splits * hkv_decode;
-  // the header, the share cuts and the append row order, then the lists (the
-  // tile list with at least 8 bytes per tile and KV head) and the partial results
+  // the header, the share cuts and the append row order, then the lists (the tile list
+  // no smaller than the 8 bytes per tile and KV head that this size has always held,
+  // which what callers compare it with may count on) and the partial results: two
+  // pieces a share, of the query rows that the fullest tile can have (17 MB for chunks
+  // of up to 16 tokens and 4 heads a KV head, 68 MB from 64 tokens)
   l.order_offset = kAlign + align_up(kShares * sizeof(int4));
   l.tiles_offset = l.order_offset + align_up((size_t)(B_append > 0 ? B_append : 0) * sizeof(int32_t));
   const size_t tiles = (size_t)(l.max_tiles / hkv_append);
@@ -623,7 +626,8 @@ MixedLayout mixed_layout(int32_t B_decode, int32_t B_append, int32_t hq, int32_t
       l.splits_offset + align_up((size_t)(B_decode > 0 ? B_decode : 0) * sizeof(int32_t));
   l.pieces_offset = align_up(l.partials_offset +
                              (B_decode > 0 ? decode_workspace_bytes(B_decode, hq, l.plan) : 0));
-  const size_t piece_rows = l.max_tiles > 0 ? (size_t)2 * kShares * atile::kRowsPerGroup : 0;
+  l.piece_rows = (max_q_len < qpb ? max_q_len : qpb) * (hq / hkv_append);
+  const size_t piece_rows = l.max_tiles > 0 ? (size_t)2 * kShares * l.piece_rows : 0;
   l.bytes = l.pieces_offset + piece_rows * (kHeadDim * sizeof(float) + sizeof(float2));
   return l;
 }
@@ -666,8 +670,9 @@ hipError_t launch_mixed(const uint16_t *q_decode, const PagedKV &kv_decode,
   m.tile_start = reinterpret_cast<int32_t *>(ws + layout.starts_offset);
   m.split_start = reinterpret_cast<int32_t *>(ws + layout.splits_offset);
   m.part.o = reinterpret_cast<float *>(ws + layout.pieces_offset);
+  m.part.rows = layout.piece_rows;
   m.part.ml = reinterpret_cast<float2 *>(
-      m.part.o + (size_t)2 * kShares * atile::kRowsPerGroup * kHeadDim);
+      m.part.o + (size_t)2 * kShares * layout.piece_rows * kHeadDim);
   m.B_append = B_append;
 
   // the fused page write (append rows only): the chunks' tokens at ctx_lens

@@ -486,3 +486,14 @@ def test_append_write_grid_limit(lib):
     assert call(2**31 - 1, 256) == _lib.RA_ERR_UNSUPPORTED    # 4.3e9 workgroups
     assert call(2**31 - 1, 64) == _lib.RA_ERR_WORKSPACE
     assert call(64, 256) == _lib.RA_ERR_WORKSPACE
+
+
+def test_append_workspace_follows_the_chunks(lib):
+    """Pieces of cut tiles hold the query rows that a tile of the call can have."""
+    f = lib.rollout_attn_append_workspace_size
+    piece = lambda rows: 2 * 256 * rows * (128 + 2) * 4
+    for T in (1, 16, 63):
+        assert piece(4 * T) < f(2, 32, 8, T) < piece(4 * T) + (64 << 10)
+    for T in (64, 65, 2048):
+        assert piece(256) < f(2, 32, 8, T) < piece(256) + (64 << 10)
+    assert piece(5 * 51) < f(1, 5, 1, 1000) < piece(255) + (64 << 10)    # 51 queries of 5 heads

@@ -152,3 +152,24 @@ def test_many_equal_rows_repeat(device, B, Hq, Hkv, ctx, T):
     ref, _ = oracle.append(sel, np.arange(len(rows) + 1) * T, np.asarray(lens)[rows], bits(k), bits(v),
                            np.repeat(lay.block_table, len(rows), 0), SCALE)
     assert_attn_close(out.cpu().numpy()[pick], ref, "many equal rows")
+
+
+@pytest.mark.parametrize("Hq,Hkv,T", [(32, 8, 1), (32, 8, 63), (32, 8, 65), (5, 1, 1), (15, 3, 52), (32, 1, 9)])
+def test_cut_tiles_stay_in_the_workspace(device, Hq, Hkv, T):
+    """A workspace of exactly the asked size: the pieces, as large as the call's fullest tile,
+    overlap nothing and reach no further."""
+    print(f"[gpu-test] append line workspace Hq={Hq} Hkv={Hkv} T={T}", flush=True)
+    w = synth.append_workload(27, 2, Hq, Hkv, lambda r, n: np.asarray([5000, 3000]),
+                              lambda r, n: np.asarray([T, T]), "append line workspace")
+    t = synth.make_tensors(w, device)
+    kv = ra.PagedKV(t.k_pool, t.v_pool, i32(w.append_table(), device))
+    size = ra.append_workspace_size(2, Hq, Hkv, T)
+    ws = torch.full((size + 4096,), 255, dtype=torch.uint8, device=device)
+    out, lse = ra.append(t.q_append, i32(w.cu_q(), device), i32(w.ctx_lens, device), kv, T, 5000 + T,
+                         SCALE, want_lse=True, workspace=ws[:size])
+    torch.cuda.synchronize()
+    assert torch.all(ws[size:] == 255), "written past the workspace"
+    ref, ref_lse = oracle.append(bits(t.q_append), w.cu_q(), w.ctx_lens, bits(t.k_pool),
+                                 bits(t.v_pool), w.append_table(), SCALE)
+    assert_attn_close(out.cpu().numpy(), ref, "append line workspace")
+    np.testing.assert_allclose(lse.cpu().numpy(), ref_lse, atol=APPEND_LSE_ATOL, rtol=0)
