@@ -143,9 +143,14 @@ const char *ra_status_string(int status);
  *               rollout_attn_decode_workspace_size(B, Hq, Hkv, max_kv_len) bytes
  *               (split partial results; contents on entry are ignored). The
  *               size is that of the fastest splits and can fall as B or
- *               max_kv_len grows; a workspace sized for a larger call of the
- *               same Hq and Hkv is always enough where 512-key splits fit it:
- *               the splits are lengthened until their partials fit.
+ *               max_kv_len grows. On a smaller workspace the splits are
+ *               lengthened until their partials fit, to 512 keys or the longer
+ *               splits that much work takes, which can change the rounding of
+ *               the results (order of fp32 sums); RA_ERR_WORKSPACE if those do
+ *               not fit either. So a workspace sized for the largest call of a
+ *               loop need not hold every smaller one (65 rows of 32768 keys over
+ *               8 KV heads: too small for 64 rows): take the largest size over
+ *               the calls to come.
  * Errors: RA_ERR_NULL, RA_ERR_SHAPE (B < 0, Hq % Hkv, max_kv_len > bt_stride*16),
  *         RA_ERR_UNSUPPORTED, RA_ERR_WORKSPACE, RA_ERR_HIP.
  */
@@ -159,7 +164,7 @@ int rollout_attn_decode(const void *q, const ra_paged_kv *kv, const int32_t *kv_
  * Decode that allocates nothing, for callers that cannot allocate device
  * memory or pass a workspace: code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc. Arguments, results and errors are
- * those of rollout_attn_decode without the workspace; the split partial
+ * those of rollout_attn_decode with a workspace of its size; the split partial
  * results go to a scratch array of RA_NOALLOC_SCRATCH_BYTES that the library
  * holds in each GPU's memory until the process ends. A call whose
  * rollout_attn_decode_workspace_size(B, Hq, Hkv, max_kv_len) exceeds

@@ -99,9 +99,11 @@ int check_decode(const void *q, const ra_paged_kv *kv, const int32_t *kv_lens, i
 }
 
 // Doubles the split length of a plan with shorter splits; false once it is the plain
-// plan's. A workspace sized for other shapes (more rows, longer rows) may hold fewer
-// slots than the shorter splits need, but then holds the plain plan's: 9 rows of up to
-// 4,096 keys over one KV head want 16 slots a row, 16 such rows 8.
+// plan's (the call's own: 512 keys, or longer with much work). A workspace sized for other
+// shapes may hold fewer slots than the shorter splits need but those of the plain plan: 9
+// rows of up to 4,096 keys over one KV head want 16 slots a row, 16 such rows 8. It may
+// hold neither, where more rows have a longer plain split: sized for 65 rows of 32,768 keys
+// over 8 KV heads (4,096-key splits), it is too small for 64 (2,048-key).
 bool coarsen_plan(ra::DecodePlan *plan, int32_t B, int32_t hkv, int32_t max_kv_len) {
   if (plan->split_tokens >= ra::decode_plan(B, hkv, max_kv_len).split_tokens) return false;
   plan->split_tokens *= 2;

@@ -101,10 +101,11 @@ int64_t split_override() {
 //   pair each instead of four in a chain (1 row of 1,000 keys, 8 KV heads: 12.4
 //   -> 7.6 us; 1 row of 4,096: 12.6 -> 8.8 us). Above that the shorter splits
 //   only add partials (2 rows of 16,000: 27.3 us with 512-key splits, 30.4 with
-//   256; 1 row of 65,000: 54 and 65 us). The longest row keeps at most
-//   kSmallSlots slots: its combine reads them in rounds (1 row of 30,000 keys, 1
-//   KV head: 17.4 us with 59 slots, 29.4 with 235; 1 row of 8,000, 2 KV heads:
-//   10.2 with 32 slots, 11.1 with 63, 13.2 with 16). Nor are there to be more than
+//   256; 1 row of 65,000: 54 and 65 us). Splits are shortened below 512 keys only as
+//   far as the longest row then has kSmallSlots slots (in 512-key splits it can have
+//   more): its combine reads them in rounds (1 row of 30,000 keys, 1 KV head: 17.4 us
+//   with 59 slots, 29.4 with 235; 1 row of 8,000, 2 KV heads: 10.2 with 32 slots, 11.1
+//   with 63, 13.2 with 16). Nor are there to be more than
 //   kSmallParts (head, slot) partials, which groups of 17 to 32 heads reach first
 //   (8 rows of 4,000 keys, 32 heads over one KV head, 8,192 partials: 17.2 -> 14.4 us;
 //   16 such rows 18.7 us in 512-key splits, 20.0 in 128-key ones, their shared-prefix

@@ -35,7 +35,12 @@
 // blocks, 16.5 blocks a share) takes 81 us queued and 107 us as a line; 8 rows
 // over 2 KV heads 692 us queued and 575 us as a line. With far more tiles than
 // CUs the line loses the sharing of K/V in the XCD's L2: 64 mixed rows 7.0 ms
-// queued and 8.0 ms as a line.
+// queued and 8.0 ms as a line. Decode rows beside the append rows do not enter the
+// rule (a mixed call's append rows get the bits of the append call): all shares come
+// before the decode splits, where queued tiles run beside them. That gains the more
+// the longer the tiles (32 decode rows of 16k with 2 rows of 256 over 12k 794 -> 574
+// us) and loses 1 to 2 % where decode is most of the call (256 such rows with 1 row of
+// 64 over 16k 2,686 -> 2,717 us); shares spread over the decode splits were slower.
 //
 // Decode splits (row, split, KV head) are queued per XCD in both modes, row by
 // row. In each queue the workgroups take the next entry of one merged order
@@ -70,9 +75,11 @@ constexpr int kCostBuckets = 4096;   // key-block counts above this share the la
 constexpr int kHeadBits = 8;         // KV heads of a call: at most 1 << kHeadBits
 constexpr int kQueues = 8;           // one work queue per XCD
 constexpr int kShares = 256;         // line mode: most shares (one per CU of an MI355X)
-constexpr int kMinShare = 4;         // line mode: fewest key blocks a share is cut to (2, 4 and 8
-                                     // measure 39, 35 and 33 us at 1 row of 30 over 3k keys and
-                                     // 44, 51 and 53 us at 1 row of 200 over 1k)
+constexpr int kMinShare = 4;         // line mode: fewest key blocks a share is cut to. More
+                                     // pieces cost merging, fewer leave compute units idle: 2, 4
+                                     // and 8 measure 39, 35 and 33 us at 1 row of 30 over 3k
+                                     // keys and 44, 51 and 53 us at 1 row of 200 over 1k; no
+                                     // value is best at both
 constexpr int kLineCost = 16;        // line mode: key blocks its partial results cost a share
 constexpr int64_t kMaxLine = 1 << 28;   // line mode: most key blocks (int32 positions)
 

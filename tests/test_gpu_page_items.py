@@ -2,9 +2,9 @@
 writes of several heads per workgroup: bit for bit the oracle's pools.
 
 A call with single tokens beside long chunks finds each page's row by a search
-over cu_new (one, two or three rounds of 64 probes here); rotated writes of many
-pages take four KV heads per workgroup, the fused write two, so the KV head counts
-leave remainders. Rows without tokens, page-aligned and unaligned starts and ends
+over cu_new (one, two or three rounds of 64 probes here); rotated writes of many full
+pages into bf16 pools take four KV heads per workgroup where four divide them, the fused
+write two, so some KV head counts leave a remainder. Rows without tokens, page-aligned and unaligned starts and ends
 are among the rows.
 """
 import numpy as np
@@ -24,8 +24,10 @@ ROWS = [
     ([1] * 70 + [500], 3),                                        # two search rounds
     ([0, 1, 15, 16, 17, 31, 33, 0, 600] + [1] * 40 + [0], 8),     # one round, edges of pages
     ([1] * 5000 + [900, 1000], 2),                                # three rounds
-    ([1] * 1000 + [500, 500], 5),                                 # search, four heads when rotated
-    ([300] * 60, 9),                                              # full grid, four heads when rotated
+    ([1] * 1000 + [500, 500], 5),                                 # search, an odd number of heads
+    ([300] * 60, 9),                                              # full grid, one head left of four
+    ([300] * 60, 8),                                              # full grid, four heads when rotated (bf16)
+    ([1] * 800 + [2000] * 4 + [1100] * 8, 8),                     # search, four heads when rotated (bf16)
 ]
 
 

@@ -1,9 +1,10 @@
 """Calls launched on a side stream with outputs and workspaces the binding allocates.
 
-The binding allocates the call's outputs and workspace with torch while the
-kernels run on the caller's stream. It records those blocks on that stream, so
-torch's caching allocator must not hand them to work on the current stream
-before the kernels are done. The test drops every reference right after each
+The kernels run on the caller's stream, and the binding allocates the call's
+outputs and workspace from that stream's own memory: torch's caching allocator then
+hands out no block that work of another stream may still use, and takes none back
+for the current stream before the kernels are done (outputs are recorded there as
+well, where the caller reads them). The test drops every reference right after each
 call and makes the default stream allocate and fill blocks of the same sizes
 meanwhile; the results must still equal the default-stream results bitwise and
 the oracle within the attention tolerance.
