@@ -500,6 +500,11 @@ __device__ __forceinline__ void append_tile(const AppendArgs &a, const AppendTil
   // mask; every wave passes the same barriers (one per block).
   const int mb = __builtin_amdgcn_readfirstlane(min(nblocks, (wave_q0 + 1) / kBlock));
   int blk = kb0;
+  // The key loop starts a few instructions after a 64-byte line: in the first half of a
+  // 32-byte fetch window (0 to 12 bytes in) the 32-row append takes 6.21 ms and the 64-row
+  // step 6.50 ms, in the second half (16 to 28 bytes in, by chance of the code before it)
+  // 6.27 and 6.56 ms.
+  asm volatile(".p2align 6");
   for (; blk < mb; ++blk) block(blk, std::false_type{});
   const bool first_wave = __builtin_amdgcn_readfirstlane(wave) == 0;
   int next = 0;
