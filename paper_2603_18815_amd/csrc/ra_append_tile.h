@@ -29,7 +29,7 @@
 // the max of the tile's first pair of pages, where an uncut tile's running max
 // starts: the weights are then rounded to bf16 as in the uncut tile (unless the
 // max moves on the way), and cutting a tile changes its result by the order of
-// fp32 sums alone (2e-7 to 5e-7 of the result's norm, 2e-3 before; 2 rows of 64..512
+// fp32 sums alone (2e-7 to 1e-6 of the result's norm, 2e-3 before; 2 rows of 64..512
 // new tokens over 2k..24k keys; 209 -> 211 us).
 #pragma once
 
